@@ -35,9 +35,10 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-# Per-source extra flags: the cross-kernel keeps its MFMA results in ordinary VGPRs (read
-# by the ALU right after), which saves the accumulator-to-VGPR moves.
-EXTRA = {"xkernel.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# Per-source extra flags: the cross-kernel and the block factorisation keep their MFMA
+# results in ordinary VGPRs (read by the ALU right after), which saves the
+# accumulator-to-VGPR moves.
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("xkernel.hip", "chol.hip")}
 
 
 def _compile(src):
