@@ -1646,7 +1646,6 @@ LSDesc ls_desc(const Layout &L) {
   return d;
 }
 
-constexpr int kLsTopkParts = 256;
 constexpr int kLsStepsPerCheck = 4;  // steps enqueued between host checks
 // Start selection with a bound (from this many candidates on): kLsPruneTop candidates of
 // largest bound are scored first, and only the candidates whose bound reaches the
@@ -1658,7 +1657,7 @@ constexpr int64_t kLsPruneDiv = 4;
 struct LSPlan {
   char *score_ws; size_t score_bytes;
   float *mu, *sigma, *ei, *acq;
-  float *pv, *sv; int64_t *pi, *si;
+  float *sv; int64_t *pi, *si;
   LSCols cur;
   uint8_t *mask;
   float *cur_acq; int32_t *active, *steps;
@@ -1688,7 +1687,6 @@ LSPlan plan_ls(Carver &cv, const gp_model &m, const LSDesc &d, int64_t M, int k)
   P.acq = cv.take<float>(rows);
   const bool prune = M >= kLsPruneMin;
   const int kp = prune ? kLsPruneTop : k;  // widest top-k taken
-  P.pv = cv.take<float>((int64_t)kLsTopkParts * kp);
   P.pi = cv.take<int64_t>((int64_t)kLsTopkParts * kp);
   P.sv = cv.take<float>(k);
   P.si = cv.take<int64_t>(k);
@@ -1805,10 +1803,10 @@ gp_status gp_local_search(const gp_model *m, const void *const *C_cols, int64_t 
       HIPCHK(launch_ls_bound(S1.mu64, S1.sens, S1.valid, mask, M, m->fstar,
                              std::sqrt(m->sv) * (1.0 + 1e-6), P.acq, P.count, s));
       const int kt = (int)std::min<int64_t>(kLsPruneTop, M);
-      HIPCHK(launch_ls_topk(P.acq, M, kt, P.pv, P.pi, kLsTopkParts, P.tv, P.ti, s));
+      HIPCHK(launch_ls_topk(P.acq, M, kt, P.pi, P.tv, P.ti, s));
       HIPCHK(launch_ls_gather_rows(d, C, P.ti, kt, P.G, mask, P.mg, s));
       HIPCHK(score_rows(P.G, mask ? P.mg : nullptr, kt, P.tacq));
-      HIPCHK(launch_ls_topk(P.tacq, kt, k, P.pv, P.pi, kLsTopkParts, P.kv, P.ki, s, P.ti));
+      HIPCHK(launch_ls_topk(P.tacq, kt, k, P.pi, P.kv, P.ki, s, P.ti));
       HIPCHK(launch_ls_compact(P.acq, M, P.kv + (k - 1), P.list, P.count, P.cap, s));
       HIPCHK(hipMemcpyAsync(hact, P.count, sizeof(int32_t), hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
@@ -1816,7 +1814,7 @@ gp_status gp_local_search(const gp_model *m, const void *const *C_cols, int64_t 
       if (cnt >= k && cnt <= P.cap) {
         HIPCHK(launch_ls_gather_rows(d, C, P.list, cnt, P.G, mask, P.mg, s));
         HIPCHK(score_rows(P.G, mask ? P.mg : nullptr, cnt, P.acq));
-        HIPCHK(launch_ls_topk(P.acq, cnt, k, P.pv, P.pi, kLsTopkParts, P.sv, P.si, s, P.list));
+        HIPCHK(launch_ls_topk(P.acq, cnt, k, P.pi, P.sv, P.si, s, P.list));
         picked = true;
       }
     }
@@ -1824,7 +1822,7 @@ gp_status gp_local_search(const gp_model *m, const void *const *C_cols, int64_t 
       if ((st = gp_score(m, C_cols, M, mask, eps_f, P.mu, P.sigma, P.ei, nullptr, P.acq, nullptr,
                          P.score_ws, P.score_bytes, stream)) != GP_OK)
         return st;
-      HIPCHK(launch_ls_topk(P.acq, M, k, P.pv, P.pi, kLsTopkParts, P.sv, P.si, s));
+      HIPCHK(launch_ls_topk(P.acq, M, k, P.pi, P.sv, P.si, s));
     }
     HIPCHK(launch_ls_gather(d, C, M, P.si, P.sv, k, P.cur, P.cur_acq, P.active, P.steps, s));
 

@@ -34,6 +34,7 @@ constexpr int kKChunk = 32;          // K* row stride granularity (contraction k
 constexpr int kRowTile = 128;        // contraction row tile; M is padded to it
 constexpr int kColTile = 128;        // contraction column tile
 constexpr int kMaxTiles = 96;        // contraction column tiles (reg + cls)
+constexpr int kLsTopkParts = 256;    // lists of the start selection (k keys of 8 bytes each)
 constexpr int kNB = 32;              // fp64 factorisation block
 
 // One parameter as the encoder sees it (device table, encode order).
@@ -223,9 +224,9 @@ struct LSCols {
   uint32_t *col[kMaxD];
 };
 // Indices (and values) of the k <= kLsMaxStarts largest of acq[0..M) (lower index
-// first on ties) into idx / v; pv, pi: parts * k scratch.
-hipError_t launch_ls_topk(const float *acq, int64_t M, int k, float *pv, int64_t *pi, int parts,
-                          float *v, int64_t *idx, hipStream_t s, const int64_t *map = nullptr);
+// first on ties) into idx / v; part: kLsTopkParts * k words of scratch.
+hipError_t launch_ls_topk(const float *acq, int64_t M, int k, int64_t *part, float *v,
+                          int64_t *idx, hipStream_t s, const int64_t *map = nullptr);
 // (map: the index of element q is map[q] rather than q)
 // ub[j] >= the acquisition value of candidate j, from its cross-kernel mean (mu64, sens),
 // validity and mask; f* and smax = sqrt(signal variance); *count = 0

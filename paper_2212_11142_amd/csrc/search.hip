@@ -15,6 +15,8 @@
 //   PERM  every exchange of the positions of two items i < j, (i, j) ascending.
 // Out-of-range neighbours are scored as copies of the current configuration with a
 // zero mask, so their acquisition value is 0 and never wins a strict comparison.
+#include <algorithm>
+
 #include "encode_param.h"
 
 namespace bgp {
@@ -31,7 +33,7 @@ __device__ __forceinline__ void ls_stage(T &dst, const T &src) {
   for (int q = threadIdx.x; q < (int)(sizeof(T) / 4); q += blockDim.x) d[q] = s[q];
 }
 
-// (value, index) order of the start selection: larger value first, lower index on ties
+// (value, index) order of a step's selection: larger value first, lower index on ties
 __device__ __forceinline__ bool ls_before(float v, int64_t i, float w, int64_t j) {
   return v > w || (v == w && i < j);
 }
@@ -65,73 +67,151 @@ __device__ __forceinline__ void ls_block_best(float &v, int64_t &i, float *sv, i
   __syncthreads();  // the slots are free again
 }
 
-// k rounds over x[lo, hi): round r takes the best element after the round r-1 pick in
-// ls_before order (no exclusion list needed). A NaN value ranks as -inf, so every index
-// can be picked and a range of at least k elements yields k picks; missing picks of a
-// shorter range are (-inf, INT64_MAX). A thread keeps its first kTopkCache elements in
-// registers; elements past those are read again in every round.
-constexpr int kTopkCache = 16;
-__device__ void ls_topk_range(const float *x, const int64_t *xi, int64_t lo, int64_t hi, int k,
-                              float *out_v, int64_t *out_i, float *sv, int64_t *si) {
-  auto load = [&](int64_t q, float &v, int64_t &i) {
-    v = __builtin_isnan(x[q]) ? -INFINITY : x[q];
-    i = xi ? xi[q] : q;
-  };
-  float cv[kTopkCache];
-  int64_t ci[kTopkCache];
-#pragma unroll
-  for (int c = 0; c < kTopkCache; ++c) {
-    const int64_t q = lo + threadIdx.x + (int64_t)c * blockDim.x;
-    cv[c] = -INFINITY;
-    ci[c] = INT64_MAX;  // an empty slot is never picked
-    if (q < hi) load(q, cv[c], ci[c]);
-  }
-  const int64_t rest = lo + (int64_t)kTopkCache * blockDim.x;
-  float pv = INFINITY;
-  int64_t pi = -1;
-  for (int r = 0; r < k; ++r) {
-    float bv = -INFINITY;
-    int64_t bi = INT64_MAX;
-    auto offer = [&](float v, int64_t i) {
-      if (i >= 0 && i != INT64_MAX && ls_before(pv, pi, v, i) && ls_before(v, i, bv, bi)) {
-        bv = v;
-        bi = i;
-      }
-    };
-#pragma unroll
-    for (int c = 0; c < kTopkCache; ++c) offer(cv[c], ci[c]);
-    for (int64_t q = rest + threadIdx.x; q < hi; q += blockDim.x) {
-      float v;
-      int64_t i;
-      load(q, v, i);
-      offer(v, i);
-    }
-    ls_block_best(bv, bi, sv, si);
-    if (threadIdx.x == 0) {
-      out_v[r] = bv;
-      out_i[r] = bi;
-    }
-    pv = bv;
-    pi = bi;
-  }
+// Start selection: the k largest of (value, index), lower index first on equal values. Both
+// are one 64-bit key whose unsigned order is the selection's: the value's bits made
+// monotone (a NaN ranks as -inf, -0 as 0) above the index's complement. 0 is no key.
+__device__ __forceinline__ uint64_t topk_key(float v, int64_t i) {
+  if (i < 0 || i > INT32_MAX) return 0;  // an empty slot
+  v = __builtin_isnan(v) ? -INFINITY : v + 0.0f;
+  const uint32_t u = __float_as_uint(v);
+  const uint32_t m = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((uint64_t)m << 32) | (0xffffffffu - (uint32_t)i);
+}
+__device__ __forceinline__ float topk_value(uint64_t k) {
+  const uint32_t m = (uint32_t)(k >> 32);
+  return k ? __uint_as_float((m & 0x80000000u) ? (m & 0x7fffffffu) : ~m) : -INFINITY;
+}
+__device__ __forceinline__ int64_t topk_index(uint64_t k) {
+  return k ? (int64_t)(0xffffffffu - (uint32_t)k) : INT64_MAX;
 }
 
-__global__ __launch_bounds__(256) void ls_topk_partial(const float *acq, const int64_t *map,
-                                                        int64_t M, int k, float *pv, int64_t *pi) {
-  __shared__ float sv[256];
-  __shared__ int64_t si[256];
+// Descending bitonic sort of P (a power of two) keys in LDS by the 256 threads of a block.
+__device__ void topk_sort(uint64_t *key, int P) {
+  for (int size = 2; size <= P; size <<= 1)
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      for (int i = threadIdx.x; i < P / 2; i += 256) {
+        const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+        const bool desc = (lo & size) == 0;
+        const uint64_t a = key[lo], b = key[hi];
+        if ((a < b) == desc) {
+          key[lo] = b;
+          key[hi] = a;
+        }
+      }
+      __syncthreads();
+    }
+}
+
+// The k best keys of each block's range of x, in descending order (0 past the range's end).
+// A block reads 1024 elements at a time and keeps those above its k-th best so far, which
+// LDS collects and sorts when it could overflow: after the first sort only few are kept.
+// (Taking the maximum k times over the range cost a block reduction per pick.)
+constexpr int kTopkBatch = 1024;
+constexpr int kTopkBuf = 2 * kTopkBatch;
+static_assert(kLsMaxStarts + kTopkBatch <= kTopkBuf, "a batch fits beside the best");
+__global__ __launch_bounds__(256) void ls_topk_partial(const float *x, const int64_t *map,
+                                                        int64_t M, int k, uint64_t *out) {
+  __shared__ uint64_t key[kTopkBuf];
+  __shared__ int cnt_s;
+  const int tid = threadIdx.x;
   const int64_t chunk = (M + gridDim.x - 1) / gridDim.x;
   const int64_t lo = (int64_t)blockIdx.x * chunk, hi = min(M, lo + chunk);
-  ls_topk_range(acq, map, lo, max(lo, hi), k, pv + (int64_t)blockIdx.x * k,
-                pi + (int64_t)blockIdx.x * k, sv, si);
+  uint64_t floor_key = 0;  // the k-th best so far (0: fewer than k)
+  if (tid == 0) cnt_s = 0;
+  __syncthreads();
+  for (int64_t base = lo; base < hi; base += kTopkBatch) {
+    uint64_t kv[kTopkBatch / 256];
+#pragma unroll
+    for (int u = 0; u < kTopkBatch / 256; ++u) {
+      const int64_t q = base + tid + 256 * u;
+      kv[u] = q < hi ? topk_key(x[q], map ? map[q] : q) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kTopkBatch / 256; ++u)
+      if (kv[u] > floor_key) key[atomicAdd(&cnt_s, 1)] = kv[u];
+    __syncthreads();
+    const int cnt = cnt_s;
+    __syncthreads();
+    if (cnt + kTopkBatch > kTopkBuf || base + kTopkBatch >= hi) {  // (uniform)
+      int P = 64;
+      while (P < cnt) P <<= 1;
+      for (int i = cnt + tid; i < P; i += 256) key[i] = 0;
+      __syncthreads();
+      topk_sort(key, P);
+      if (tid == 0) cnt_s = min(cnt, k);
+      floor_key = cnt >= k ? key[k - 1] : 0;
+      __syncthreads();
+    }
+  }
+  const int have = cnt_s;
+  for (int i = tid; i < k; i += 256) out[(int64_t)blockIdx.x * k + i] = i < have ? key[i] : 0;
 }
 
-__global__ __launch_bounds__(256) void ls_topk_final(const float *pv, const int64_t *pi, int n,
-                                                      int k, float *v, int64_t *idx) {
-  __shared__ float sv[256];
-  __shared__ int64_t si[256];
-  ls_topk_range(pv, pi, 0, n, k, v, idx, sv, si);
+__device__ __forceinline__ uint64_t lane_key(uint64_t x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+  return (uint64_t)lo | ((uint64_t)hi << 32);
 }
+template <int kRor>
+__device__ __forceinline__ uint64_t max_row_ror(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, 0x120 + kRor, 15, 15, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), 0x120 + kRor, 15, 15, true);
+  const uint64_t y = (uint64_t)lo | ((uint64_t)hi << 32);
+  return y > x ? y : x;
+}
+// The largest key of a wavefront, in every lane: rotations within rows of 16 lanes, then
+// the four rows' results.
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t x) {
+  x = max_row_ror<8>(x);
+  x = max_row_ror<4>(x);
+  x = max_row_ror<2>(x);
+  x = max_row_ror<1>(x);
+  const uint64_t a = max(lane_key(x, 0), lane_key(x, 16)), b = max(lane_key(x, 32), lane_key(x, 48));
+  return max(a, b);
+}
+
+// Merges the blocks' descending lists (kTopkParts at most, k keys each, staged in LDS):
+// lane l of the first wavefront holds the heads of lists l, l + 64, ..; each pick is a
+// maximum over the wavefront and the winner's list moves on.
+constexpr int kTopkParts = kLsTopkParts;
+__global__ __launch_bounds__(1024) void ls_topk_final(const uint64_t *part, int parts, int k,
+                                                      float *v, int64_t *idx) {
+  extern __shared__ uint64_t lists[];
+  for (int i = threadIdx.x; i < parts * k; i += 1024) lists[i] = part[i];
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  constexpr int kOwn = kTopkParts / 64;
+  uint64_t head[kOwn];
+  int pos[kOwn];
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int l = lane + 64 * u;
+    head[u] = l < parts ? lists[l * k] : 0;
+    pos[u] = 0;
+  }
+  uint64_t mine = 0;  // lane r keeps pick r (k <= 64)
+  for (int r = 0; r < k; ++r) {
+    uint64_t best = head[0];
+#pragma unroll
+    for (int u = 1; u < kOwn; ++u) best = max(best, head[u]);
+    best = wave_max_key(best);
+    if (lane == r) mine = best;
+    if (best == 0) break;  // the lists are exhausted (uniform)
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u)
+      if (head[u] == best) {  // keys are unique: one lane, one list
+        const int l = lane + 64 * u;
+        ++pos[u];
+        head[u] = pos[u] < k ? lists[l * k + pos[u]] : 0;
+      }
+  }
+  if (lane < k) {
+    v[lane] = topk_value(mine);
+    idx[lane] = topk_index(mine);
+  }
+}
+static_assert(kLsMaxStarts <= 64, "one lane per pick");
 
 // cur[s] = configuration start[s] of the candidate columns; cur_acq[s] its value;
 // every start active, no moves yet (k <= M, so every start is an index below M)
@@ -149,10 +229,9 @@ __global__ __launch_bounds__(256) void ls_gather(const LSDesc dsc0, const LSCols
   if (s >= k) return;
   const int64_t j = start[s];
   if (j < 0 || j >= M) return;
-  for (int p = 0; p < dsc.d; ++p) {
-    const int wd = dsc.words[p];
-    for (int q = threadIdx.x; q < wd; q += blockDim.x)
-      cur.col[p][(int64_t)s * wd + q] = C.col[p][j * wd + q];
+  for (int w = threadIdx.x; w < dsc.W; w += blockDim.x) {  // one word per thread
+    const int p = dsc.wparam[w], wd = dsc.words[p], q = w - dsc.woff[p];
+    cur.col[p][(int64_t)s * wd + q] = C.col[p][j * wd + q];
   }
   if (threadIdx.x == 0) {
     cur_acq[s] = start_v[s];
@@ -454,11 +533,23 @@ hipError_t launch_ls_gather_rows(const LSDesc &d, const LSCols &C, const int64_t
   return hipGetLastError();
 }
 
-hipError_t launch_ls_topk(const float *acq, int64_t M, int k, float *pv, int64_t *pi, int parts,
-                          float *v, int64_t *idx, hipStream_t s, const int64_t *map) {
-  if (k < 1 || k > kLsMaxStarts || parts < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(ls_topk_partial, dim3(parts), dim3(256), 0, s, acq, map, M, k, pv, pi);
-  hipLaunchKernelGGL(ls_topk_final, dim3(1), dim3(256), 0, s, pv, pi, parts * k, k, v, idx);
+hipError_t launch_ls_topk(const float *acq, int64_t M, int k, int64_t *part, float *v,
+                          int64_t *idx, hipStream_t s, const int64_t *map) {
+  if (k < 1 || k > kLsMaxStarts || M < 1 || M > INT32_MAX) return hipErrorInvalidValue;
+  // a block per batch of elements, up to the lists that one wavefront can merge
+  const int parts = (int)std::min<int64_t>((M + kTopkBatch - 1) / kTopkBatch, kTopkParts);
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ls_topk_final),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             kTopkParts * kLsMaxStarts * (int)sizeof(uint64_t));
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  uint64_t *lists = reinterpret_cast<uint64_t *>(part);
+  hipLaunchKernelGGL(ls_topk_partial, dim3(parts), dim3(256), 0, s, acq, map, M, k, lists);
+  hipLaunchKernelGGL(ls_topk_final, dim3(1), dim3(1024), sizeof(uint64_t) * parts * k, s, lists,
+                     parts, k, v, idx);
   return hipGetLastError();
 }
 

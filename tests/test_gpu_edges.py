@@ -57,3 +57,22 @@ def test_block_factorisation_failing_pivot(dup):
         assert e.status == 2 and f"pivot {dup} " in str(e)
     else:
         assert model.export("L")[dup, dup] <= 1e-6
+
+
+@pytest.mark.parametrize("k", [1, 8, 63, 64])
+@pytest.mark.parametrize("M", [1, 3, 64, 65, 1023, 1024, 1025, 2049, 5000, 65535])
+def test_start_selection(M, k):
+    """The starts of a search are the k largest values, lower index first on ties (a mask
+    makes many equal zeros), at the edges of the selection's batches and block counts."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload("C1", 65536, n=20)
+    space, model = _fit(w)
+    Cc = [c[:M].contiguous() for c in gp.to_device_columns(space, w.C)]
+    mask = (torch.arange(M, device="cuda") % 3 == 1).to(torch.uint8)
+    acq = gp.score(model, Cc, mask=mask)["acq"].cpu().numpy()
+    out = gp.local_search(model, Cc, mask=mask, n_starts=k, max_steps=0)
+    want = np.lexsort((np.arange(M), -acq))[:min(k, M)]
+    assert np.array_equal(out["start_index"].cpu().numpy(), want)
+    assert np.array_equal(out["acq"].cpu().numpy(), acq[want])
