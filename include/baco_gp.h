@@ -385,7 +385,8 @@ size_t gp_cot_workspace_bytes(const gp_space *space, int32_t n_trees, const int3
  *               depth-first walk that takes children in ascending value order); only
  *               read during the call
  *  workspace    >= gp_cot_workspace_bytes bytes, 256-B aligned; holds the chain's
- *               tables (8 bytes per leaf) and must outlive the handle
+ *               tables (its keys, 8 bytes per leaf, and hash buckets of them, 12.8
+ *               bytes per leaf) and must outlive the handle
  * GP_E_INVALID names the first leaf out of range or out of order. */
 gp_status gp_cot_create(const gp_space *space, int32_t n_trees, const int32_t *tree_size,
                         const int32_t *tree_params, const int64_t *n_leaves,

@@ -2181,17 +2181,20 @@ gp_status gp_hyperfit(const gp_space *space, const void *const *X_cols, int32_t 
 struct gp_cot {
   bgp::CotDesc h;             // host copy of the descriptor
   bgp::CotDesc *d_desc = nullptr;
-  uint64_t *d_keys = nullptr;
+  uint64_t *d_keys = nullptr, *d_buckets = nullptr;
 };
 
 namespace {
 struct CotPlan {
-  CotDesc *desc; uint64_t *keys; unsigned long long *bad;
+  CotDesc *desc; uint64_t *keys, *buckets; unsigned long long *bad;
+  int64_t nbuck;
 };
-CotPlan plan_cot(Carver &cv, int64_t total_leaves) {
+CotPlan plan_cot(Carver &cv, const CotDesc &D, int64_t total_leaves) {
   CotPlan P{};
   P.desc = cv.take<CotDesc>(1);
   P.keys = cv.take<uint64_t>(std::max<int64_t>(total_leaves, 1));
+  for (int t = 0; t < D.n_trees; ++t) P.nbuck += D.nbuck[t];
+  P.buckets = cv.take<uint64_t>(P.nbuck * kCotBucket);
   P.bad = cv.take<unsigned long long>(1);
   return P;
 }
@@ -2235,6 +2238,8 @@ gp_status cot_desc(const gp_space *space, int32_t n_trees, const int32_t *tree_s
     D.koff[t] = total;
     D.nleaves[t] = n_leaves[t];
     total += n_leaves[t];
+    D.nbuck[t] = (n_leaves[t] + kCotFill - 1) / kCotFill;
+    D.boff[t] = t > 0 ? D.boff[t - 1] + D.nbuck[t - 1] : 0;
     int bits = 0;
     unsigned __int128 range = 1;
     for (int l = k - 1; l >= 0; --l) {
@@ -2270,7 +2275,7 @@ size_t gp_cot_workspace_bytes(const gp_space *space, int32_t n_trees, const int3
   int64_t total = 0;
   if (cot_desc(space, n_trees, tree_size, tree_params, n_leaves, D, total) != GP_OK) return 0;
   Carver cv;
-  plan_cot(cv, total);
+  plan_cot(cv, D, total);
   return cv.off;
 }
 
@@ -2288,16 +2293,18 @@ gp_status gp_cot_create(const gp_space *space, int32_t n_trees, const int32_t *t
     for (int t = 0; t < n_trees; ++t)
       if (!leaves || !leaves[t]) return fail(GP_E_INVALID, "leaves of tree " + std::to_string(t) + " are NULL");
     Carver meas;
-    plan_cot(meas, total);
+    plan_cot(meas, c->h, total);
     if ((st = check_ws(workspace, ws_bytes, meas.off)) != GP_OK) return st;
     Carver cv;
     cv.base = static_cast<char *>(workspace);
     cv.size = ws_bytes;
-    const CotPlan P = plan_cot(cv, total);
+    const CotPlan P = plan_cot(cv, c->h, total);
     hipStream_t s = static_cast<hipStream_t>(stream);
     c->d_desc = P.desc;
     c->d_keys = P.keys;
+    c->d_buckets = P.buckets;
     HIPCHK(hipMemcpyAsync(P.desc, &c->h, sizeof(CotDesc), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemsetAsync(P.buckets, 0xff, sizeof(uint64_t) * kCotBucket * P.nbuck, s));
     // keys of every tree; the first bad leaf (out of range or out of order) is reported
     for (int t = 0; t < n_trees; ++t) {
       unsigned long long bad = ~0ull;
@@ -2309,6 +2316,7 @@ gp_status gp_cot_create(const gp_space *space, int32_t n_trees, const int32_t *t
         return fail(GP_E_INVALID, "tree " + std::to_string(t) + ", leaf " + std::to_string(bad) +
                                       ": a value index out of range or leaves not in strictly "
                                       "increasing lexicographic order");
+      HIPCHK(launch_cot_hash(c->h, t, P.keys, P.buckets, s));
     }
     HIPCHK(hipStreamSynchronize(s));
     *out = c.release();
@@ -2345,7 +2353,8 @@ gp_status gp_cot_member(const gp_cot *c, const void *const *cols, int64_t M, uin
       return fail(GP_E_INVALID, "column " + std::to_string(p) + " (in a tree) is NULL");
     cc.col[p] = const_cast<void *>(cols[p]);
   }
-  HIPCHK(launch_cot_member(c->d_desc, c->d_keys, cc, M, mask, static_cast<hipStream_t>(stream)));
+  HIPCHK(launch_cot_member(c->d_desc, c->d_keys, c->d_buckets, cc, M, mask,
+                           static_cast<hipStream_t>(stream)));
   return GP_OK;
 }
 

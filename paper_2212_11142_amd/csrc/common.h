@@ -414,7 +414,12 @@ struct CotDesc {
   int32_t tparam[kMaxD];
   int64_t koff[kCotMaxTrees];     // first key of tree t
   int64_t nleaves[kCotMaxTrees];
+  // membership: buckets of kCotBucket keys hashed from tree t's, nbuck[t] of them from
+  // bucket boff[t]
+  int64_t boff[kCotMaxTrees], nbuck[kCotMaxTrees];
 };
+constexpr int kCotBucket = 8;     // keys of a hash bucket (64 bytes)
+constexpr int kCotFill = 5;       // keys per bucket on average at most
 struct CotCols {
   void *col[kMaxD];
 };
@@ -424,8 +429,11 @@ hipError_t launch_cot_keys(const CotDesc *dd, int tree, const int32_t *leaves, i
                            uint64_t *keys, unsigned long long *bad, hipStream_t s);
 hipError_t launch_cot_sample(const CotDesc *dd, const uint64_t *keys, int64_t M, uint64_t seed,
                              uint64_t offset, const CotCols &out, hipStream_t s);
-hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const CotCols &cols,
-                             int64_t M, uint8_t *mask, hipStream_t s);
+// hashes tree t's keys into its buckets (all slots of which hold kCotEmpty before)
+hipError_t launch_cot_hash(const CotDesc &hd, int t, const uint64_t *keys, uint64_t *buckets,
+                           hipStream_t s);
+hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const uint64_t *buckets,
+                             const CotCols &cols, int64_t M, uint8_t *mask, hipStream_t s);
 
 // ------------------------------------------------ random-forest feasibility (forest.hip)
 // Hidden constraints (Sec. 4.2): a classification forest of CART trees on bootstrap

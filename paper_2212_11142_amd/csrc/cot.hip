@@ -150,39 +150,88 @@ __global__ __launch_bounds__(256) void cot_sample_k(const CotDesc *dd, const uin
   }
 }
 
+// Membership is a hash lookup: a binary search of the sorted keys is a chain of dependent
+// loads, each from another line of a table far larger than the L2 (9.3 M leaves: 24 steps,
+// 141 us per 1 M configurations; with two levels of sampled keys before it, one of them in
+// LDS, 83 us, bound by 11 L2 requests and 3.3 misses per configuration; this takes 34 us,
+// one missing line per configuration). A bucket is half a 128-byte line; it holds up to
+// kCotBucket keys, kCotFill on average at most, and a full bucket's further keys go to the
+// next one, so a lookup reads buckets until it finds the key or a free slot.
+constexpr uint64_t kCotEmpty = ~0ull;  // (a key of 64 one bits is looked up in the key table)
+__device__ __forceinline__ int64_t cot_bucket(uint64_t key, int64_t n) {
+  uint64_t h = key * 0x9E3779B97F4A7C15ull;  // 2^64 / golden ratio
+  h ^= h >> 32;
+  h *= 0x9E3779B97F4A7C15ull;
+  return (int64_t)__umul64hi(h, (uint64_t)n);
+}
+
+__global__ __launch_bounds__(256) void cot_hash_k(const uint64_t *keys, int64_t n, int64_t nb,
+                                                   uint64_t *buckets) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t key = keys[i];
+  if (key == kCotEmpty) return;
+  int64_t b = cot_bucket(key, nb);
+  // n < nb kCotBucket keys: a free slot exists (nb + 1 buckets are looked at in the end)
+  for (int64_t step = 0; step <= nb; ++step) {
+    unsigned long long *s = reinterpret_cast<unsigned long long *>(buckets + b * kCotBucket);
+    for (int q = 0; q < kCotBucket; ++q)
+      if (s[q] == kCotEmpty && atomicCAS(s + q, kCotEmpty, (unsigned long long)key) == kCotEmpty) return;
+    b = b + 1 == nb ? 0 : b + 1;
+  }
+}
+
+constexpr int kCotGroup = 8;  // parameters whose values are loaded together
 __global__ __launch_bounds__(256) void cot_member_k(const CotDesc *dd, const uint64_t *keys,
-                                                     const CotCols cols0, int64_t M,
-                                                     uint8_t *mask) {
-  __shared__ CotDesc D;
-  __shared__ CotCols cols;
-  stage(D, *dd);
-  stage(cols, cols0);
-  __syncthreads();
+                                                     const uint64_t *buckets, const CotCols cols0,
+                                                     int64_t M, uint8_t *mask) {
+  // The descriptor's fields are the same for every lane: read as constant memory (never
+  // written by this kernel) they are scalar loads.
+  typedef __attribute__((address_space(4))) const CotDesc cdesc;
+  typedef __attribute__((address_space(1))) const int32_t gint;
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  const cdesc &D = *(const cdesc *)dd;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= M) return;
   bool ok = true;
   for (int t = 0; t < D.n_trees && ok; ++t) {
     uint64_t key = 0;
-    for (int l = 0; l < D.tcount[t]; ++l) {
-      const int p = D.tparam[D.tstart[t] + l];
-      const int32_t v = static_cast<const int32_t *>(cols.col[p])[j] - D.lo[p];
-      ok = ok && v >= 0 && v < D.dim[p];
-      key |= (uint64_t)((uint32_t)v & D.fmask[p]) << D.shift[p];
+    const int t0 = D.tstart[t], tc = D.tcount[t];
+    for (int l0 = 0; l0 < tc; l0 += kCotGroup) {
+      int32_t v[kCotGroup];
+#pragma unroll
+      for (int u = 0; u < kCotGroup; ++u)
+        if (l0 + u < tc) v[u] = ((const gint *)cols0.col[D.tparam[t0 + l0 + u]])[j];
+#pragma unroll
+      for (int u = 0; u < kCotGroup; ++u)
+        if (l0 + u < tc) {
+          const int p = D.tparam[t0 + l0 + u];
+          const int64_t w = (int64_t)v[u] - D.lo[p];
+          ok = ok && w >= 0 && w < D.dim[p];
+          key |= (uint64_t)((uint32_t)w & D.fmask[p]) << D.shift[p];
+        }
     }
     if (!ok) break;
-    // lower bound of key in the tree's sorted keys
-    const uint64_t *kt = keys + D.koff[t];
-    int64_t lo = 0, n = D.nleaves[t];
-    while (n > 0) {
-      const int64_t h = n >> 1;
-      if (kt[lo + h] < key) {
-        lo += h + 1;
-        n -= h + 1;
-      } else {
-        n = h;
-      }
+    if (key == kCotEmpty) {  // the largest key there is: the last leaf or none
+      ok = keys[D.koff[t] + D.nleaves[t] - 1] == key;
+      continue;
     }
-    ok = lo < D.nleaves[t] && kt[lo] == key;
+    const int64_t nb = D.nbuck[t];
+    const uint64_t *bt = buckets + D.boff[t] * kCotBucket;
+    int64_t b = cot_bucket(key, nb);
+    ok = false;
+    for (int64_t step = 0; step < nb; ++step) {
+      const u64x2 *s = reinterpret_cast<const u64x2 *>(bt + b * kCotBucket);
+      bool free_slot = false;
+#pragma unroll
+      for (int q = 0; q < kCotBucket / 2; ++q) {
+        const u64x2 e = s[q];
+        ok = ok || e[0] == key || e[1] == key;
+        free_slot = free_slot || e[0] == kCotEmpty || e[1] == kCotEmpty;
+      }
+      if (ok || free_slot) break;
+      b = b + 1 == nb ? 0 : b + 1;
+    }
   }
   mask[j] = ok ? 1 : 0;
 }
@@ -205,11 +254,21 @@ hipError_t launch_cot_sample(const CotDesc *dd, const uint64_t *keys, int64_t M,
   return hipGetLastError();
 }
 
-hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const CotCols &cols,
-                             int64_t M, uint8_t *mask, hipStream_t s) {
+hipError_t launch_cot_hash(const CotDesc &hd, int t, const uint64_t *keys, uint64_t *buckets,
+                           hipStream_t s) {
+  const int64_t n = hd.nleaves[t];
+  if (n <= 0) return hipSuccess;
+  if (n >= hd.nbuck[t] * kCotBucket) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(cot_hash_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                     keys + hd.koff[t], n, hd.nbuck[t], buckets + hd.boff[t] * kCotBucket);
+  return hipGetLastError();
+}
+
+hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const uint64_t *buckets,
+                             const CotCols &cols, int64_t M, uint8_t *mask, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   hipLaunchKernelGGL(cot_member_k, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, dd, keys,
-                     cols, M, mask);
+                     buckets, cols, M, mask);
   return hipGetLastError();
 }
 

@@ -76,3 +76,55 @@ def test_start_selection(M, k):
     want = np.lexsort((np.arange(M), -acq))[:min(k, M)]
     assert np.array_equal(out["start_index"].cpu().numpy(), want)
     assert np.array_equal(out["acq"].cpu().numpy(), acq[want])
+
+
+@pytest.mark.parametrize("sizes", [[1], [2], [4], [5], [6], [7], [39], [41], [300000],
+                                   [1, 5, 5000, 200000]])
+def test_chain_membership_tables(sizes):
+    """Membership against numpy at the edges of its hash buckets: one bucket partly filled
+    (wrapping onto itself), one key more than it holds on average, many buckets, several
+    trees; first and last leaves, their neighbours and values out of range among the
+    configurations."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    from workloads import Param
+    rng = np.random.default_rng(7)
+    params = [Param(f"i{q}", "int", lo=-3, hi=1 << 19) for q in range(2 * len(sizes))]
+    leaves, keep = [], []
+    for s in sizes:
+        rows = np.unique(rng.integers(0, 1 << 19, size=(2 * s + 8, 2)), axis=0)
+        rows = rows[np.sort(rng.choice(len(rows), s, replace=False))].astype(np.int32)
+        leaves.append(rows)
+        keep.append(set(map(tuple, rows.tolist())))
+    chain = gp.Chain(gp.Space(params), [[2 * t, 2 * t + 1] for t in range(len(sizes))], leaves)
+    M = 4099
+    cols, want = [], np.ones(M, bool)
+    for t, rows in enumerate(leaves):
+        pick = rows[rng.integers(0, len(rows), M)].astype(np.int64)
+        pick[:2] = rows[[0, -1]]
+        pick[2:4] = rows[[0, -1]] + [[0, -1], [0, 1]]
+        off = rng.random(M) < 0.2
+        pick[off, 1] += rng.integers(-2, 3, off.sum())
+        pick[rng.random(M) < 0.02, 0] += 1 << 19
+        want &= np.array([tuple(r) in keep[t] for r in pick.tolist()])
+        cols += [pick[:, 0] - 3, pick[:, 1] - 3]   # raw values: lo + index
+    got = chain.member([torch.from_numpy(c.astype(np.int32)).cuda() for c in cols]).cpu().numpy()
+    assert np.array_equal(got.astype(bool), want)
+
+
+def test_chain_membership_all_ones_key():
+    """A key of 64 one bits (two 32-bit fields at their last value) is a member only if it is
+    a leaf."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    from workloads import Param
+    params = [Param(f"c{q}", "cat", levels=65536) for q in range(4)]
+    top = [65535] * 4
+    for rows in ([[0, 1, 2, 3], top], [[0, 1, 2, 3], [65535, 65535, 65535, 65534]]):
+        chain = gp.Chain(gp.Space(params), [[0, 1, 2, 3]], [np.array(rows, np.int32)])
+        conf = np.array([top, [0, 1, 2, 3], [65535, 65535, 65535, 65534]], np.int32)
+        cols = [torch.from_numpy(np.ascontiguousarray(conf[:, q])).cuda() for q in range(4)]
+        want = [1 if c in rows else 0 for c in conf.tolist()]
+        assert chain.member(cols).cpu().tolist() == want
