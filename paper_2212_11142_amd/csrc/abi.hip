@@ -2366,12 +2366,14 @@ struct gp_forest {
   bgp::ForestDesc *d_desc = nullptr;
   bgp::ForestNode *d_nodes = nullptr;
   int32_t *d_nnodes = nullptr;
+  bgp::ForestTrees trees{};
 };
 
 namespace {
 struct ForestPlan {
   ForestDesc *desc; ParamEnc *penc; double *table; uint32_t *codes; uint8_t *valid;
-  double *X; int32_t *idx, *tmp, *aux, *nnodes; ForestNode *nodes;
+  double *X, *val; uint16_t *rank; int32_t *aux, *nnodes, *nd, *lofs, *bstart; ForestNode *nodes;
+  uint64_t *pack;
 };
 ForestPlan plan_forest(Carver &cv, const Layout &L, int n, int F, int T) {
   ForestPlan P{};
@@ -2383,8 +2385,12 @@ ForestPlan plan_forest(Carver &cv, const Layout &L, int n, int F, int T) {
   P.codes = cv.take<uint32_t>((int64_t)n * L.R);
   P.valid = cv.take<uint8_t>(n);
   P.X = cv.take<double>((int64_t)F * n);
-  P.idx = cv.take<int32_t>((int64_t)T * n);
-  P.tmp = cv.take<int32_t>((int64_t)T * n);
+  P.val = cv.take<double>((int64_t)F * n);
+  P.rank = cv.take<uint16_t>((int64_t)F * n);
+  P.nd = cv.take<int32_t>(F);
+  P.pack = cv.take<uint64_t>((int64_t)T * 2 * n);
+  P.lofs = cv.take<int32_t>(T);
+  P.bstart = cv.take<int32_t>(T + 1);
   P.aux = cv.take<int32_t>((int64_t)T * 2 * n * 3);
   return P;
 }
@@ -2467,9 +2473,29 @@ gp_status gp_forest_fit(const gp_space *space, const void *const *X_cols, int32_
     CotCols cc{};
     for (int p = 0; p < L.d; ++p) cc.col[p] = const_cast<void *>(X_cols[p]);
     HIPCHK(launch_forest_features(P.desc, cc, n, n, P.X, s));
-    HIPCHK(launch_forest_train(P.desc, n_trees, P.X, feasible, P.idx, P.tmp, P.nodes, P.aux,
+    HIPCHK(launch_forest_ranks(P.X, n, f->h.F, P.rank, P.val, P.nd, s));
+    HIPCHK(launch_forest_train(P.desc, f->h, P.rank, P.val, P.nd, feasible, P.nodes, P.pack, P.aux,
                                P.nnodes, s));
+    // prediction's batches: consecutive trees whose nodes fit its LDS together
+    std::vector<int32_t> nn((size_t)n_trees), lofs((size_t)n_trees), bstart;
+    HIPCHK(hipMemcpyAsync(nn.data(), P.nnodes, sizeof(int32_t) * n_trees, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const int64_t room = forest_tree_words(f->h.F);
+    int64_t used = 0, most = 1;
+    for (int32_t q = 0; q < n_trees; ++q) {
+      if (q == 0 || used + nn[q] > room) {
+        bstart.push_back(q);
+        used = 0;
+      }
+      lofs[q] = (int32_t)used;
+      used += nn[q];
+      most = std::max(most, used);
+    }
+    bstart.push_back(n_trees);
+    HIPCHK(hipMemcpyAsync(P.lofs, lofs.data(), sizeof(int32_t) * n_trees, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(P.bstart, bstart.data(), sizeof(int32_t) * bstart.size(), hipMemcpyHostToDevice, s));
+    HIPCHK(hipStreamSynchronize(s));
+    f->trees = ForestTrees{P.pack, P.nnodes, P.lofs, P.bstart, (int32_t)bstart.size() - 1, most, P.val, P.nd};
     f->d_desc = P.desc;
     f->d_nodes = P.nodes;
     f->d_nnodes = P.nnodes;
@@ -2493,7 +2519,8 @@ gp_status gp_forest_predict(const gp_forest *f, const void *const *C_cols, int64
   if (st != GP_OK) return st;
   CotCols cc{};
   for (int p = 0; p < f->h.d; ++p) cc.col[p] = const_cast<void *>(C_cols[p]);
-  HIPCHK(launch_forest_predict(f->d_desc, f->h, f->d_nodes, cc, M, ei, mask, eps_f, p_feas, acq,
+  HIPCHK(launch_forest_predict(f->d_desc, f->h, f->trees, cc, M, ei, mask, eps_f, p_feas, acq,
+                               stream_cus(static_cast<hipStream_t>(stream)),
                                static_cast<hipStream_t>(stream)));
   return GP_OK;
 }

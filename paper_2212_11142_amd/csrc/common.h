@@ -456,14 +456,34 @@ struct ForestNode {      // internal: feature >= 0, x_f <= val goes to child `le
 // features [F][ld] (column-major) of `count` configurations given as raw columns
 hipError_t launch_forest_features(const ForestDesc *dd, const CotCols &cols, int64_t count,
                                   int64_t ld, double *X, hipStream_t s);
-// one workgroup per tree; idx, tmp: [n_trees][n]; nodes [n_trees][cap]; aux [n_trees][cap][3]
-hipError_t launch_forest_train(const ForestDesc *dd, int n_trees, const double *X,
-                               const uint8_t *y, int32_t *idx, int32_t *tmp, ForestNode *nodes,
-                               int32_t *aux, int32_t *n_nodes, hipStream_t s);
+// per feature: ranks of the observations [F][n], distinct values [F][n], their number [F]
+hipError_t launch_forest_ranks(const double *X, int32_t n, int32_t F, uint16_t *rank, double *val,
+                               int32_t *nd, hipStream_t s);
+// one workgroup per tree; nodes, pack (prediction's form): [n_trees][cap], aux [n_trees][cap][3]
+hipError_t launch_forest_train(const ForestDesc *dd, const ForestDesc &hd, const uint16_t *rank,
+                               const double *val, const int32_t *nd, const uint8_t *y,
+                               ForestNode *nodes, uint64_t *pack, int32_t *aux, int32_t *n_nodes,
+                               hipStream_t s);
+// The trees as prediction reads them: batches that fit tree_words nodes of LDS together.
+struct ForestTrees {
+  const uint64_t *pack;
+  const int32_t *n_nodes, *lofs, *bstart;
+  int32_t nbatch;
+  int64_t tree_words;
+  const double *val;
+  const int32_t *nd;
+};
+constexpr size_t kForestLds = 156 * 1024;  // prediction: trees and ranks
+// wavefronts per prediction workgroup at most: their ranks take up to 64 KB of the LDS
+inline int forest_predict_waves(int F) { return F <= 32 ? 16 : (F <= 64 ? 8 : 4); }
+inline int64_t forest_tree_words(int F) {
+  return (int64_t)(kForestLds - (size_t)forest_predict_waves(F) * F * 64 * sizeof(uint16_t)) / 8;
+}
+static_assert((kForestLds - 64 * 1024) / 8 >= 2 * kMaxN, "the largest tree fits");
 // p = mean over trees of the leaf values; acq = ei * p if allowed and p > eps_f else 0
-hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestNode *nodes,
+hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestTrees &tr,
                                  const CotCols &cols, int64_t M, const float *ei,
-                                 const uint8_t *mask, float eps_f, float *p, float *acq,
+                                 const uint8_t *mask, float eps_f, float *p, float *acq, int cus,
                                  hipStream_t s);
 
 // fp64 linear algebra (linalg.hip)

@@ -128,3 +128,41 @@ def test_chain_membership_all_ones_key():
         cols = [torch.from_numpy(np.ascontiguousarray(conf[:, q])).cuda() for q in range(4)]
         want = [1 if c in rows else 0 for c in conf.tolist()]
         assert chain.member(cols).cpu().tolist() == want
+
+
+@pytest.mark.parametrize("n,trees,depth,min_split", [
+    (1, 3, 4, 2), (2, 5, 4, 1), (63, 4, 20, 2), (64, 4, 20, 2), (65, 4, 20, 2), (66, 7, 3, 9),
+    (130, 3, 40, 2), (1025, 3, 40, 2), (2049, 2, 40, 2), (4096, 2, 40, 2)])
+def test_forest_sizes(n, trees, depth, min_split):
+    """Trees against the oracle, node for node, where the growth changes form: nodes of up to
+    64 samples and above, ranks of many distinct values, wide levels, odd tree counts; and
+    predictions against walking the returned trees (the same sum in the same order)."""
+    import torch
+
+    from oracle import gp_forest as of
+    from paper_2212_11142_amd import gp
+    w = make_workload("C1", 700, n=n)
+    rng = np.random.default_rng(n)
+    feas = (rng.random(n) < 0.6).astype(np.uint8)
+    space = gp.Space(w.space)
+    X = gp.to_device_columns(space, w.X)
+    forest = gp.Forest(space, X, torch.from_numpy(feas).cuda(), n_trees=trees, max_depth=depth,
+                  min_split=min_split, seed=11)
+    ref = of.fit_forest(w.space, w.X, feas, trees, 11, depth, min_split)
+    got = [forest.tree(t) for t in range(trees)]
+    for t in range(trees):
+        r = ref[t]
+        val = [th if f >= 0 else v for f, th, v in zip(r.feature, r.threshold, r.value)]
+        for a, b in zip(got[t], (r.feature, r.left, val)):
+            assert np.array_equal(a, np.array(b))
+    F = of.features(w.space, w.C)
+    want = np.zeros(700)
+    for feat, left, val in got:
+        k = np.zeros(700, np.int64)
+        while np.any(feat[k] >= 0):
+            go = feat[k] >= 0
+            x = F[np.arange(700), np.maximum(feat[k], 0)]
+            k = np.where(go, left[k] + np.where(x <= val[k], 0, 1), k)
+        want += val[k]
+    p, _ = forest.predict(gp.to_device_columns(space, w.C))
+    assert np.array_equal(p.cpu().numpy(), (want / trees).astype(np.float32))
