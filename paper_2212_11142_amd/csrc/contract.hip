@@ -222,6 +222,117 @@ __global__ __launch_bounds__(64 * kWaves, 2) void contract_split(const CArgs a) 
   }
 }
 
+// The same contraction for few rows (a local-search step, small batches): contract_split's
+// 128 x 128 tiles would leave most compute units without a workgroup and run its chunks one
+// memory latency after another. Here a workgroup takes 16 rows of a column tile, one
+// wavefront per 16-column sub-tile, and four k-chunks at a time: the next four are loaded
+// into registers (whole rows of 512 bytes) while the present ones are multiplied from LDS.
+// Every output is formed by the same operations in the same order (k-chunks, the three
+// partial products, the sub-tiles' squares), so the results are bit-identical.
+constexpr int kFewRows = 16;
+constexpr int kFewWaves = kColTile / 16;
+constexpr int kFewAhead = 4;                          // chunks per load group
+constexpr int kFewThreads = 64 * kFewWaves;
+constexpr int kFewLanes = 8 * kFewAhead;              // threads per row (16 bytes each)
+constexpr int kFewStep = kFewThreads / kFewLanes;     // rows per load instruction
+constexpr int kFewLoads = (kFewRows + kColTile) / kFewStep;
+static_assert(kFewRows % kFewStep == 0 && kColTile % kFewStep == 0, "whole instructions");
+__global__ __launch_bounds__(kFewThreads) void contract_few(const CArgs a) {
+  // [chunk][rows of A, then rows of B^T][32 words, swizzled as contract_split's tiles]
+  constexpr int kPlane = (kFewRows + kColTile) * kLdsStride;
+  __shared__ __attribute__((aligned(16))) float buf[kFewAhead * kPlane];
+  __shared__ float xs[kFewWaves][kFewRows][17];
+  __shared__ float red[kWC][kFewRows];
+  const int rb = blockIdx.x / a.ntiles, t = blockIdx.x - rb * a.ntiles;
+  const CTile tl = a.tiles[t];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, fg = lane >> 4;
+  const int64_t row0 = (int64_t)rb * kFewRows;
+  const int lin_sub = tl.lin >= 0 ? (tl.lin & ~15) : -1, c0 = 16 * w;
+  const int kneed = c0 == lin_sub ? tl.kend : (c0 < tl.ncol) ? tl.tri0 + c0 + 16 : 0;
+  const int nk = tl.kend / kKChunk;
+  typedef float floatx4g __attribute__((ext_vector_type(4)));
+  // thread: 16-byte slot tid % kFewLanes of a row's load group (chunk slot / 8)
+  const int slot = tid % kFewLanes, lrow = tid / kFewLanes;
+  const float *src[kFewLoads];
+  float *dst[kFewLoads];
+#pragma unroll
+  for (int u = 0; u < kFewLoads; ++u) {
+    const int r = kFewStep * u + lrow;  // row of the plane
+    src[u] = (r < kFewRows ? reinterpret_cast<const float *>(a.A) + (row0 + r) * a.lda
+                           : reinterpret_cast<const float *>(a.Bt) + (int64_t)(tl.bcol + r - kFewRows) * a.lda) +
+             4 * (slot & 7);
+    dst[u] = buf + (slot >> 3) * kPlane +
+             (r < kFewRows ? lds_off(r, slot & 7) : kFewRows * kLdsStride + lds_off(r - kFewRows, slot & 7));
+  }
+  floatx4g st[kFewLoads];
+  auto load = [&](int k0) {  // (past the end the last chunk again)
+    const int o = min(k0 + (slot >> 3), nk - 1) * kKChunk;
+#pragma unroll
+    for (int u = 0; u < kFewLoads; ++u) st[u] = *reinterpret_cast<const floatx4g *>(src[u] + o);
+  };
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  load(0);
+  for (int k0 = 0; k0 < nk; k0 += kFewAhead) {
+#pragma unroll
+    for (int u = 0; u < kFewLoads; ++u) *reinterpret_cast<floatx4g *>(dst[u]) = st[u];
+    __syncthreads();
+    load(k0 + kFewAhead);
+#pragma unroll
+    for (int u = 0; u < kFewAhead; ++u) {
+      if (k0 + u < nk && (k0 + u) * kKChunk < kneed) {  // wave-uniform
+        const float *As = buf + u * kPlane, *Bs = As + kFewRows * kLdsStride;
+        const half8 ah = *(const half8 *)&As[lds_off(fr, fg)], al = *(const half8 *)&As[lds_off(fr, 4 + fg)];
+        const half8 bh = *(const half8 *)&Bs[lds_off(c0 + fr, fg)];
+        const half8 bl = *(const half8 *)&Bs[lds_off(c0 + fr, 4 + fg)];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, acc, 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  }
+  const float cs = a.cscale[tl.bcol + c0 + fr];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float x = acc[v] * cs;
+    xs[w][fg * 4 + v][fr] = x;
+    if (c0 + fr == tl.lin) a.lin[row0 + fg * 4 + v] = x;
+  }
+  __syncthreads();
+  if (w < kWC) {  // column wave w of contract_split: sub-tiles w, w + kWC, ..
+    float sq[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < kCS; ++k) {
+        const int sub = kWC * k + w;
+        const float x = xs[sub][fg * 4 + v][fr];
+        const float keep = (16 * sub + fr == tl.lin) ? 0.f : 1.f;
+        s = fmaf(x * keep, x, s);
+      }
+      sq[v] = s;
+    }
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sq[v] += __shfl_xor(sq[v], off);
+    if (fr == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[w][fg * 4 + v] = sq[v];
+    }
+  }
+  __syncthreads();
+  if (tid < kFewRows) {
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < kWC; ++c) v += red[c][tid];
+    a.part[(int64_t)t * a.rows + row0 + tid] = v;
+  }
+}
+
 __device__ __forceinline__ float norm_cdf_f(float z) { return 0.5f * erfcf(-z * 0.70710678118654752f); }
 
 __device__ __forceinline__ float ei_f32(float mu, float sigma, float fstar) {
@@ -939,6 +1050,11 @@ __global__ __launch_bounds__(256) void gather_rows_split(const _Float16 *src, in
 
 }  // namespace
 
+// contract_few while its workgroups are at most one per compute unit. Measured (us, with
+// timing events; contract_few / contract_split): 16 tiles of 128 x 128 at n = 512 10.8 /
+// 17.1, 24 at n = 1500 20 / 35, 32 at n = 128 7.1 / 9.0; 64 at n = 512 16.5 / 17.1, 64 at
+// n = 128 10.3 / 9.4, 96 at n = 1500 48 / 38.
+constexpr int64_t kFewGrid = 256 / (kRowTile / kFewRows);
 hipError_t launch_contract(const CArgs &a, hipStream_t s) {
   const int64_t grid = (int64_t)a.nrowtiles * a.ntiles;
   if (grid <= 0) return hipSuccess;
@@ -948,6 +1064,11 @@ hipError_t launch_contract(const CArgs &a, hipStream_t s) {
     // a linear column lies in a sub-tile of its own, past the triangular columns
     if (tl.lin >= 0 && (!a.lin || tl.lin >= kColTile || (tl.lin & ~15) < tl.ncol))
       return hipErrorInvalidValue;
+  }
+  if (grid <= kFewGrid) {
+    hipLaunchKernelGGL(contract_few, dim3((unsigned)(grid * (kRowTile / kFewRows))),
+                       dim3(kFewThreads), 0, s, a);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(contract_split, dim3((unsigned)grid), dim3(64 * kWaves), 0, s, a);
   return hipGetLastError();

@@ -166,3 +166,21 @@ def test_forest_sizes(n, trees, depth, min_split):
         want += val[k]
     p, _ = forest.predict(gp.to_device_columns(space, w.C))
     assert np.array_equal(p.cpu().numpy(), (want / trees).astype(np.float32))
+
+
+@pytest.mark.parametrize("name", ["C3", "C4"])
+def test_few_rows_bit_identical(name):
+    """Batches small enough for the few-rows contraction and the one-block cross-kernel give
+    the bits that the same candidates have inside a batch that takes the large tiles (every
+    column tile, the classifier's dense column among them)."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload(name, 16384)
+    _, model = _fit(w)
+    C = gp.to_device_columns(gp.Space(w.space), w.C)
+    big = gp.score(model, C)
+    for M in (1, 127, 128, 129, 300, 511, 640, 1025):
+        small = gp.score(model, [c[:M].contiguous() for c in C])
+        for k in ("sigma", "p_feas"):
+            assert torch.equal(small[k], big[k][:M]), (k, M)
