@@ -102,36 +102,70 @@ __global__ __launch_bounds__(256) void hyp_terms_k(const uint32_t *codes, int32_
 }
 
 // ------------------------------------------------------------------------------ Gram
-__device__ __forceinline__ double hyp_r2(const HypArgs &a, const double *w, int64_t idx,
-                                         int64_t nn) {
-  double r2 = 0.0;
-  for (int p = 0; p < a.d; ++p) r2 = fma(a.T[(int64_t)p * nn + idx], w[p], r2);
-  return r2;
+// r^2 of 16 settings and 16 pairs at a time is a matrix product, r2[b][pair] = sum_p
+// w[b][p] T[p][pair] with w = exp(-2 log l), taken on fp64 MFMA: a pair's terms are loaded
+// once for the 16 settings (they are the batch's largest data: 20 MB at d = 20, nf = 359,
+// read from beyond the L2). v_mfma_f64_16x16x4f64 takes A[row l & 15][k l >> 4] and
+// B[k l >> 4][col l & 15] from lane l and leaves D[(l >> 4) + 4 v][l & 15] in register v.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int kHypSets = 16;  // settings per wavefront
+// Lane l's w operand of k-step s: entry p = 4 s + (l >> 4) of setting b0 + (l & 15).
+__device__ __forceinline__ double hyp_w(const HypArgs &a, int b, int B, int p) {
+  return (p < a.d && b < B) ? exp(-2.0 * a.theta[(int64_t)b * a.theta_ld + p]) : 0.0;
 }
 
-// Setting b's Gram matrix K (rows 0..nf-1 of its plane) and the identity rows below it
-// (rows nf..2nf-1, whose factorisation panels give L^-1); the first workgroup of a plane
-// also resets its status (1 for an inactive setting, which is skipped).
-__global__ __launch_bounds__(256) void hyp_gram_k(const HypArgs a, double *K) {
-  __shared__ double w[kMaxD];
-  const int b = blockIdx.y;
-  const bool inactive = a.active && !a.active[b];
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.info[b] = inactive ? 1 : 0;
-  if (inactive) return;
-  const double *th = a.theta + (int64_t)b * a.theta_ld;
-  if (threadIdx.x < a.d) w[threadIdx.x] = exp(-2.0 * th[threadIdx.x]);
-  __syncthreads();
-  const int64_t nn = (int64_t)a.nf * a.nf;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= nn) return;
-  const int i = (int)(idx / a.nf), j = (int)(idx - (int64_t)i * a.nf);
-  const double s = clamp_exp(th[a.d]);
-  const double r2 = hyp_r2(a, w, idx, nn), r = sqrt(r2);
-  double k = s * (1.0 + kSqrt5 * r + (5.0 / 3.0) * r2) * exp(-kSqrt5 * r);
-  if (i == j) k += a.noise_floor + clamp_exp(th[a.d + 1]);
-  double *Kb = K + (int64_t)b * a.sA;
-  Kb[(int64_t)i * a.ld + j] = k;
-  Kb[(int64_t)(a.nf + i) * a.ld + j] = i == j ? 1.0 : 0.0;
+// Row i = blockIdx.x of the Gram matrices of settings 16 blockIdx.y ..: columns up to the
+// end of its 32-wide diagonal block (the factorisation reads no block above the diagonal),
+// and of the identity rows below, whose factorisation panels give L^-1, the columns from
+// that block on. The first row's workgroup also resets the settings' status (1 for an
+// inactive one, which is skipped). KS: k-steps (d <= 4 KS). 64 settings at nf = 359, d = 20:
+// 87 -> 34 us (one thread per entry and setting, over both triangles and all of I, before);
+// what is left is the writes and two transcendental functions per entry.
+template <int KS>
+__global__ __launch_bounds__(256) void hyp_gram_k(const HypArgs a, int B, double *K) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, fr = lane & 15, fg = lane >> 4;
+  const int b0 = blockIdx.y * kHypSets, i = blockIdx.x, nf = a.nf;
+  if (i == 0 && threadIdx.x < kHypSets && b0 + threadIdx.x < B) {
+    const int b = b0 + threadIdx.x;
+    a.info[b] = (a.active && !a.active[b]) ? 1 : 0;
+  }
+  double wop[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) wop[s] = hyp_w(a, b0 + fr, B, 4 * s + fg);
+  double sv[4], nv[4];
+  bool on[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int b = b0 + fg + 4 * v;
+    on[v] = b < B && !(a.active && !a.active[b]);
+    const double *th = a.theta + (int64_t)min(b, B - 1) * a.theta_ld;
+    sv[v] = clamp_exp(th[a.d]);
+    nv[v] = a.noise_floor + clamp_exp(th[a.d + 1]);
+  }
+  const int64_t nn = (int64_t)nf * nf;
+  const int blk0 = i & ~(kNB - 1), cend = min(nf, blk0 + kNB);
+  for (int j0 = 16 * w; j0 < cend; j0 += 64) {
+    const int j = j0 + fr, jc = min(j, nf - 1);
+    double top[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      top[s] = 4 * s + fg < a.d ? a.T[(int64_t)(4 * s + fg) * nn + (int64_t)i * nf + jc] : 0.0;
+    doublex4 r2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) r2 = __builtin_amdgcn_mfma_f64_16x16x4f64(wop[s], top[s], r2, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double r = sqrt(r2[v]);
+      double k = sv[v] * (1.0 + kSqrt5 * r + (5.0 / 3.0) * r2[v]) * exp(-kSqrt5 * r);
+      if (i == j) k += nv[v];
+      if (on[v] && j < cend) K[(int64_t)(b0 + fg + 4 * v) * a.sA + (int64_t)i * a.ld + j] = k;
+    }
+  }
+  for (int q = w; q < kHypSets && b0 + q < B; q += 4) {
+    if (a.active && !a.active[b0 + q]) continue;
+    double *Er = K + (int64_t)(b0 + q) * a.sA + (int64_t)(nf + i) * a.ld;
+    for (int j = blk0 + lane; j < nf; j += 64) Er[j] = i == j ? 1.0 : 0.0;
+  }
 }
 
 // ----------------------------------------------------------------------------- value
@@ -228,69 +262,97 @@ __global__ __launch_bounds__(256) void hyp_alpha_k(const HypArgs a, const double
 }
 
 // -------------------------------------------------------------------------- gradient
-// Launch plane (b, chunk): pairs i >= j in a grid-stride loop; every pair's coefficient
-// C = w_ij (alpha_i alpha_j - K^-1_ij) dk/dr^2 (w_ij = 2 off the diagonal) multiplies
-// T_p for the chunk's CH lengthscales; chunk 0 also sums the output-scale and noise
-// terms. Partial sums per block go to `part`, summed in block order by hyp_grad_final_k.
-__global__ __launch_bounds__(256) void hyp_grad_k(const HypArgs a, const double *Kinv,
-                                                   const double *alpha, double *part) {
-  __shared__ double w[kMaxD];
-  __shared__ double red[4];
-  const int b = blockIdx.y, chunk = blockIdx.z, tid = threadIdx.x;
-  if ((a.active && !a.active[b]) || a.info[b]) return;
-  const double *th = a.theta + (int64_t)b * a.theta_ld;
-  if (tid < a.d) w[tid] = exp(-2.0 * th[tid]);
-  __syncthreads();
-  const int nf = a.nf;
-  const double s = clamp_exp(th[a.d]);
+// A wavefront takes 16 settings and 16 pairs i >= j at a time. r2 comes out of MFMA with the
+// pairs as rows, so register v of a lane holds setting l & 15 and pair (l >> 4) + 4 v; the
+// pair's coefficient C = w_ij (alpha_i alpha_j - K^-1_ij) dk/dr^2 (w_ij = 2 off the
+// diagonal) is then already the A operand of the second product, grad[b][p] += sum_pair
+// C[b][pair] T[p][pair], whose B operand is the same terms, turned in LDS. The output-scale
+// and noise terms are summed beside it. Partial sums per workgroup (its wavefronts in order)
+// go to `part`, summed in block order by hyp_grad_final_k.
+// PT: 16-wide tiles of parameters (d <= 16 PT). 64 settings at nf = 359, d = 20: 302 -> 37 us
+// (each thread read a pair's terms for one setting, 660 MB in all, before).
+constexpr int kGradPairs = 16;
+template <int PT>
+__global__ __launch_bounds__(256) void hyp_grad_k(const HypArgs a, int B, const double *Kinv,
+                                                   const double *alpha, double *part, int nchunks) {
+  constexpr int KS = 4 * PT;
+  __shared__ double tt[4][16 * PT][kGradPairs + 1];  // terms [p][pair] of each wavefront
+  __shared__ double red[4][kHypSets][16 * PT + 2];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, fr = lane & 15, fg = lane >> 4;
+  const int b0 = blockIdx.y * kHypSets, b = b0 + fr, nf = a.nf;
+  const bool on = b < B && !(a.active && !a.active[b]) && !a.info[min(b, B - 1)];
+  double wop[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) wop[s] = hyp_w(a, b, B, 4 * s + fg);
+  const double *th = a.theta + (int64_t)min(b, B - 1) * a.theta_ld;
+  const double sv = clamp_exp(th[a.d]);
+  const double *Ki = Kinv + (int64_t)min(b, B - 1) * a.sA, *al = alpha + (int64_t)min(b, B - 1) * nf;
   const int64_t nn = (int64_t)nf * nf, npairs = (int64_t)nf * (nf + 1) / 2;
-  const double *Ki = Kinv + (int64_t)b * a.sA, *al = alpha + (int64_t)b * nf;
-  const int p0 = chunk * CH;
-  double acc[CH];
+  doublex4 acc[PT];
 #pragma unroll
-  for (int c = 0; c < CH; ++c) acc[c] = 0.0;
+  for (int q = 0; q < PT; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
   double acc_s = 0.0, acc_n = 0.0;
-  // With all lengthscales in one chunk, a pair's d terms are loaded once, for r^2 and
-  // for the sums (same operations in the same order as the two-pass form).
-  const bool one_chunk = a.d <= CH;
-  for (int64_t q = (int64_t)blockIdx.x * 256 + tid; q < npairs; q += (int64_t)gridDim.x * 256) {
-    int i, j;
-    pair_of(q, i, j);
-    const int64_t idx = (int64_t)i * nf + j;
-    double tv[CH];
-    double r2 = 0.0;
-    if (one_chunk) {
+  // (every wavefront runs the same number of rounds: the pairs past the end have C = 0)
+  const int64_t step = (int64_t)gridDim.x * 4 * kGradPairs;
+  const int64_t q0 = ((int64_t)blockIdx.x * 4 + w) * kGradPairs;
+  for (int64_t q = q0; q < npairs; q += step) {
+    int pi, pj;
+    pair_of(min(q + fr, npairs - 1), pi, pj);
+    const int64_t idx = (int64_t)pi * nf + pj;
+    double top[KS];
 #pragma unroll
-      for (int c = 0; c < CH; ++c) tv[c] = c < a.d ? a.T[(int64_t)c * nn + idx] : 0.0;
+    for (int s = 0; s < KS; ++s) top[s] = 4 * s + fg < a.d ? a.T[(int64_t)(4 * s + fg) * nn + idx] : 0.0;
+    doublex4 r2 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int c = 0; c < CH; ++c)
-        if (c < a.d) r2 = fma(tv[c], w[c], r2);
-    } else {
-      r2 = hyp_r2(a, w, idx, nn);
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-        tv[c] = p0 + c < a.d ? a.T[(int64_t)(p0 + c) * nn + idx] : 0.0;
+    for (int s = 0; s < KS; ++s) {
+      r2 = __builtin_amdgcn_mfma_f64_16x16x4f64(top[s], wop[s], r2, 0, 0, 0);
+      tt[w][4 * s + fg][fr] = top[s];
     }
-    const double r = sqrt(r2);
-    const double e = exp(-kSqrt5 * r);
-    const double dk = -(5.0 / 6.0) * s * (1.0 + kSqrt5 * r) * e;
-    const double wt = (i == j) ? 1.0 : 2.0;
-    const double G = al[i] * al[j] - Ki[(int64_t)i * a.ld + j];
-    const double C = wt * G * dk;
+    double C[4];
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (p0 + c < a.d) acc[c] = fma(C, tv[c], acc[c]);
-    if (chunk == 0) {
-      const double kf = s * (1.0 + kSqrt5 * r + (5.0 / 3.0) * r2) * e;
-      acc_s = fma(wt * G, kf, acc_s);
+    for (int v = 0; v < 4; ++v) {
+      const int i = __shfl(pi, fg + 4 * v), j = __shfl(pj, fg + 4 * v);
+      const bool in = on && q + fg + 4 * v < npairs;
+      const double x = r2[v], r = sqrt(x);
+      const double e = exp(-kSqrt5 * r);
+      const double dk = -(5.0 / 6.0) * sv * (1.0 + kSqrt5 * r) * e;
+      const double wt = (i == j) ? 1.0 : 2.0;
+      const double G = in ? al[i] * al[j] - Ki[(int64_t)i * a.ld + j] : 0.0;
+      const double kf = sv * (1.0 + kSqrt5 * r + (5.0 / 3.0) * x) * e;
+      C[v] = in ? wt * G * dk : 0.0;
+      if (in) acc_s = fma(wt * G, kf, acc_s);
       if (i == j) acc_n += G;
     }
-  }
-  double *out = part + (((int64_t)b * gridDim.z + chunk) * gridDim.x + blockIdx.x) * (CH + 2);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // tt is this wavefront's own
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int c = 0; c < CH + 2; ++c) {
-    const double v = block_sum(c < CH ? acc[c] : (c == CH ? acc_s : acc_n), red);
-    if (tid == 0) out[c] = v;
+    for (int t = 0; t < PT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(C[v], tt[w][16 * t + fr][fg + 4 * v], acc[t], 0, 0, 0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  acc_s += __shfl_xor(acc_s, 16);
+  acc_s += __shfl_xor(acc_s, 32);
+  acc_n += __shfl_xor(acc_n, 16);
+  acc_n += __shfl_xor(acc_n, 32);
+#pragma unroll
+  for (int t = 0; t < PT; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[w][fg + 4 * v][16 * t + fr] = acc[t][v];
+  if (fg == 0) {
+    red[w][fr][16 * PT] = acc_s;
+    red[w][fr][16 * PT + 1] = acc_n;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kHypSets * (16 * PT + 2); e += 256) {
+    const int r = e / (16 * PT + 2), c = e - r * (16 * PT + 2);
+    if (b0 + r >= B) continue;
+    const double v = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c];
+    double *out = part + ((int64_t)(b0 + r) * nchunks * gridDim.x + blockIdx.x) * (CH + 2);
+    if (c >= 16 * PT) out[CH + c - 16 * PT] = v;
+    else if (c < a.d) out[(int64_t)(c / CH) * gridDim.x * (CH + 2) + c % CH] = v;
   }
 }
 
@@ -598,9 +660,14 @@ hipError_t launch_hyp_terms(const uint32_t *codes, int32_t R, const TermDesc *td
 
 hipError_t launch_hyp_gram(const HypArgs &a, int B, double *K, hipStream_t s) {
   if (B < 1 || B > kHypBatch || a.d > kMaxD || a.nf < 1) return hipErrorInvalidValue;
-  const int64_t nn = (int64_t)a.nf * a.nf;
-  hipLaunchKernelGGL(hyp_gram_k, dim3((unsigned)((nn + 255) / 256), (unsigned)B), dim3(256), 0, s,
-                     a, K);
+  const dim3 grid((unsigned)a.nf, (unsigned)((B + kHypSets - 1) / kHypSets));
+  switch ((a.d + 7) / 8) {
+    case 0: case 1: hipLaunchKernelGGL(hyp_gram_k<2>, grid, dim3(256), 0, s, a, B, K); break;
+    case 2: hipLaunchKernelGGL(hyp_gram_k<4>, grid, dim3(256), 0, s, a, B, K); break;
+    case 3: hipLaunchKernelGGL(hyp_gram_k<6>, grid, dim3(256), 0, s, a, B, K); break;
+    case 4: hipLaunchKernelGGL(hyp_gram_k<8>, grid, dim3(256), 0, s, a, B, K); break;
+    default: hipLaunchKernelGGL(hyp_gram_k<16>, grid, dim3(256), 0, s, a, B, K); break;
+  }
   return hipGetLastError();
 }
 
@@ -624,9 +691,13 @@ hipError_t launch_hyp_grad(const HypArgs &a, int B, const double *Kinv, const do
   if (B < 1 || B > kHypBatch || grad_ld < a.d + 2) return hipErrorInvalidValue;
   const int nchunks = std::max((a.d + CH - 1) / CH, 1);
   const int64_t npairs = (int64_t)a.nf * (a.nf + 1) / 2;
-  const int nblk = (int)std::min<int64_t>(kHypGradBlocks, (npairs + 255) / 256);
-  hipLaunchKernelGGL(hyp_grad_k, dim3((unsigned)nblk, (unsigned)B, (unsigned)nchunks), dim3(256), 0,
-                     s, a, Kinv, alpha, part);
+  const int nblk = (int)std::min<int64_t>(kHypGradBlocks, (npairs + 4 * kGradPairs - 1) / (4 * kGradPairs));
+  const dim3 grid((unsigned)nblk, (unsigned)((B + kHypSets - 1) / kHypSets));
+  switch ((a.d + 15) / 16) {
+    case 0: case 1: hipLaunchKernelGGL(hyp_grad_k<1>, grid, dim3(256), 0, s, a, B, Kinv, alpha, part, nchunks); break;
+    case 2: hipLaunchKernelGGL(hyp_grad_k<2>, grid, dim3(256), 0, s, a, B, Kinv, alpha, part, nchunks); break;
+    default: hipLaunchKernelGGL(hyp_grad_k<4>, grid, dim3(256), 0, s, a, B, Kinv, alpha, part, nchunks); break;
+  }
   hipLaunchKernelGGL(hyp_grad_final_k, dim3((unsigned)B, (unsigned)(a.d + 2)), dim3(128), 0, s, a,
                      part, nblk, nchunks, grad, grad_ld);
   return hipGetLastError();

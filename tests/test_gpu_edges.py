@@ -184,3 +184,31 @@ def test_few_rows_bit_identical(name):
         small = gp.score(model, [c[:M].contiguous() for c in C])
         for k in ("sigma", "p_feas"):
             assert torch.equal(small[k], big[k][:M]), (k, M)
+
+
+@pytest.mark.parametrize("d,n,count", [(1, 1, 1), (1, 2, 16), (7, 15, 17), (8, 16, 3), (9, 17, 33),
+                                       (16, 33, 5), (17, 31, 15), (24, 65, 2), (25, 40, 64),
+                                       (32, 50, 65), (33, 35, 4), (64, 48, 3)])
+def test_log_posterior_shapes(d, n, count):
+    """Objective and gradient at the edges of the matrix-product tiles: 16 settings, 16
+    pairs, 4-wide steps and 16-wide tiles of parameters. Tolerances: fp64 sums of up to n^2
+    terms behind a factorisation with noise 1e-2 or more (condition below 1e5)."""
+    import torch
+
+    from oracle import gp_hyper as gh
+    from paper_2212_11142_amd import gp
+    from workloads import Param
+    rng = np.random.default_rng(d * 1000 + n)
+    params = [Param(f"r{q}", "real") if q % 3 else Param(f"c{q}", "cat", levels=4) for q in range(d)]
+    X = [rng.random(n) if p.kind == "real" else rng.integers(0, 4, n).astype(np.int32) for p in params]
+    y, feas = rng.normal(size=n), np.ones(n, np.uint8)
+    theta = rng.uniform(-1.0, 1.0, size=(count, d + 2))
+    theta[:, d + 1] = rng.uniform(np.log(1e-2), 0.0, size=count)
+    space = gp.Space(params)
+    out = gp.log_posterior(space, gp.to_device_columns(space, X), torch.from_numpy(y).cuda(),
+                           torch.from_numpy(feas).cuda(), torch.from_numpy(theta).cuda(), (1.5, 1.0))
+    T, yf = gh.hyper_data(params, X, y, feas)
+    for b in range(count):
+        rv, rg = gh.log_posterior(T, yf, theta[b], (1.5, 1.0), 1e-6)
+        assert abs(out["value"][b].item() - rv) <= 1e-10 * max(abs(rv), 1.0)
+        assert np.abs(out["grad"][b].cpu().numpy() - rg).max() <= 1e-9 * max(np.abs(rg).max(), 1.0)
