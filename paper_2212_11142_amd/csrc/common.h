@@ -198,7 +198,8 @@ struct RArgs {
 constexpr int kRefineSplitGroups = 16;
 constexpr int kRefineColRange = 64;
 // More than kRefineBlockMin flagged candidates take the block path: fp64 MFMA over
-// groups of kRefineBlockRows candidates and column tiles of kRefineBlockCols.
+// groups of candidates (the largest models: kRefineBlockRows candidates and column tiles of
+// kRefineBlockCols).
 constexpr int kRefineBlockMin = 4096;
 constexpr int kRefineBlockRows = 64;
 constexpr int kRefineBlockCols = 256;

@@ -411,8 +411,8 @@ __device__ __forceinline__ ValueRow value_row(const EArgs &a, int64_t j) {
 }
 
 // The value model's outputs of candidate j (NaN when invalid; left to the fp64
-// recomputation when flagged), then the flagged candidates compacted, one atomic per
-// wavefront. Every thread of the block calls it (the compaction uses a ballot).
+// recomputation when flagged), then the flagged candidates compacted. Every thread of the
+// 256-thread block calls it (the compaction uses ballots and a barrier).
 __device__ __forceinline__ void epilogue_value_row(const EArgs &a, int64_t j, const ValueRow &r) {
   bool flag = false;
   if (j < a.M) {
@@ -430,14 +430,22 @@ __device__ __forceinline__ void epilogue_value_row(const EArgs &a, int64_t j, co
       a.ei[j] = ei_f32(r.mu, sigma, fstar);
     }
   }
+  // one atomic per workgroup (a dense batch flags every candidate, and an atomic per
+  // wavefront on the one counter took 49 us for 262,144 of them)
+  __shared__ int wcnt[4], wbase;
   const uint64_t bal = __ballot(flag);
-  if (bal) {
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((unsigned long long)bal) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(a.refine_count, __popcll(bal));
-    base = __shfl(base, leader);
-    if (flag) a.refine_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)j;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane == 0) wcnt[wv] = __popcll(bal);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int n = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+    if (n > 0) wbase = atomicAdd(a.refine_count, n);
+  }
+  __syncthreads();
+  if (flag) {
+    int at = wbase + __popcll(bal & ((1ull << lane) - 1ull));
+    for (int w = 0; w < wv; ++w) at += wcnt[w];
+    a.refine_list[at] = (int32_t)j;
   }
 }
 
@@ -683,49 +691,60 @@ __global__ __launch_bounds__(256) void refine_finish(const RArgs a, const float 
   refine_store(a, pwork, a.list[q], a.mup[g * a.cb + c], ssq);
 }
 
-// Block path of the refinement, for many flagged candidates (dense batches near the
-// data flag most of them): a work item is a group of 64 flagged candidates and a tile of
-// 256 columns of B = L_f^-T, run by a persistent workgroup of 16 wavefronts. Per
-// 16-observation chunk, eight staging wavefronts compute the 64 x 16 fp64 kernel values
-// and load the 16 x 256 block of B into one LDS buffer while eight compute wavefronts
-// accumulate V += K B on fp64 MFMA from the other buffer (each 16 candidates x 128
-// columns; column blocks wholly left of the chunk, or wholly past n_f, are skipped, as B
-// is upper triangular); one barrier per chunk swaps the buffers. Two wavefronts of each
-// role share a SIMD, so that one's latency is covered by the other's work. The
-// candidates' codes are staged in LDS per item, alpha and the weights once; a staging
-// wavefront reads its observations' codes through the scalar cache (they are the same
-// for all its lanes). The tile's squared row norms go to part64; the last tile (whose
-// k-range covers all n_f observations) also forms mu = K alpha. refine_block_finish sums
-// the tiles in order.
-constexpr int kRbK = 16;                     // observations per chunk
-constexpr int kRbBS = kRefineBlockCols + 8;  // LDS row stride of the B block (doubles)
-constexpr int kRbKS = kRbK + 1;              // LDS row stride of the kernel block
-constexpr int kRbRoleWaves = 8;              // compute wavefronts = staging wavefronts
-constexpr int kRbWaves = 2 * kRbRoleWaves;
-constexpr int kRbObs = kRbK / kRbRoleWaves;  // observations per staging lane and chunk
-constexpr int kRbCols = kRefineBlockCols / 2;  // columns per compute wavefront
-constexpr int kRbKsD = kRefineBlockRows * kRbKS, kRbBsD = kRbK * kRbBS;  // doubles per buffer
-constexpr size_t kRbFixedBytes =
-    sizeof(double) * (2 * kRbKsD + 2 * kRbBsD + 4 * kRefineBlockRows + kRefineBlockRows);
-constexpr size_t kRbMaxLds = 160 * 1024 - 2048;  // dynamic LDS (the weights take the rest)
-static_assert(sizeof(Weights64) <= 2048, "weights in LDS");
-static_assert(kRbK % kRbRoleWaves == 0 && kRbRoleWaves == 8, "roles");
+// Block path of the refinement, for many flagged candidates (dense batches near the data flag
+// most of them): V = K B for groups of 32 flagged candidates, B = L_f^-T, on fp64 MFMA. A
+// workgroup of 8 wavefronts keeps V's accumulators (each wavefront owns some of its 16-column
+// blocks) and alternates between two phases per 64 observations: all threads compute the
+// chunk's 32 x 64 fp64 kernel values into LDS (and add them to mu, each with alpha), then
+// every wavefront multiplies them with its columns of B, read from L2 as MFMA operands (B is
+// upper triangular: blocks left of the observations are skipped). For narrow models two
+// workgroups share a compute unit, so that one's kernel values (vector ALU) run beside the
+// other's products (matrix cores). refine_block_finish takes the row norms and means.
+// Before, two roles in one workgroup met at a barrier every 16 observations
+// (refine_block_tall below). Measured, refinement stage, before / now: 262,144 candidates at
+// n_f = 180 568 / 474 us, 160,662 at n_f = 500 1957 / 1344 us, 262,144 at n_f = 700 4569 /
+// 3866 us. At n_f = 180 a chunk takes about 5,300 cycles of kernel values and 5,500 of
+// products per workgroup, of which the matrix cores are busy for 3,400.
+constexpr int kRpRows = 32, kRpK = 64, kRpWaves = 8, kRpThreads = 64 * kRpWaves;
+constexpr int kRpStride = kRpK + 2;             // LDS row stride of the kernel values
+constexpr int kRpSets = kRpThreads / kRpRows;   // observations evaluated side by side
+constexpr int kRpObs = kRpK / kRpSets;          // observations per thread and chunk
+constexpr int kRpMaxBlocks = 8;                 // column blocks per wavefront at most
+constexpr int kRpMaxCols = 16 * kRpWaves * kRpMaxBlocks;
+constexpr size_t kRpMaxLds = 150 * 1024;
+// LDS: kernel values, partial sums, two groups' candidate codes and the codes of `obs`
+// observations (numeric ones as fp64)
+inline size_t rp_lds_bytes(int n_num, int n_int, int obs) {
+  return sizeof(double) * (size_t)(kRpRows * kRpStride + kRpSets * kRpRows + kRpWaves * kRpRows +
+                                   n_num * (2 * kRpRows + obs)) +
+         sizeof(uint32_t) * (size_t)n_int * (2 * kRpRows + obs);
+}
+// Observations kept in LDS: all of them where two workgroups still share a compute unit (no
+// staging between chunks then), else one chunk's.
+constexpr size_t kRpShareLds = 78 * 1024;
+inline int rp_obs(int n_f, int n_num, int n_int) {
+  const int all = (n_f + kRpK - 1) / kRpK * kRpK;
+  return rp_lds_bytes(n_num, n_int, all) <= kRpShareLds ? all : kRpK;
+}
+// column blocks per wavefront for n_f <= kRpMaxCols columns
+inline int rp_blocks(int n_f) { return n_f <= 256 ? 2 : (n_f <= 512 ? 4 : kRpMaxBlocks); }
 
-// r2_f64 of one configuration (words a(q)) against U observations (words b(u, q)), with
-// the same operations in the same order for each of them; the U chains give the ALU
-// independent work and share the reads of a(q) and of the weights.
-template <int U, class GA, class GB>
-__device__ __forceinline__ void r2xu_f64(const GA &a, const GB &b, const Weights64 &w,
-                                         double (&r2)[U]) {
+// r2_f64 of one configuration against U observations, with the same operations in the same
+// order for each of them; the U chains give the ALU independent work and share the reads of
+// the configuration's words and of the weights. an(q) / bn(u, q): numeric codes as fp64,
+// a(q) / b(u, q): the other words (by their word number).
+template <int U, class AN, class BN, class GA, class GB>
+__device__ __forceinline__ void r2xu_f64(const AN &an, const BN &bn, const GA &a, const GB &b,
+                                         const Weights64 &w, double (&r2)[U]) {
 #pragma unroll
   for (int u = 0; u < U; ++u) r2[u] = 0.0;
   // (unrolled so that the reads of several words are in flight together)
 #pragma unroll 4
   for (int q = 0; q < w.n_num; ++q) {
-    const double av = (double)__uint_as_float(a(q)), wq = w.num_w[q];
+    const double av = an(q), wq = w.num_w[q];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double d = av - (double)__uint_as_float(b(u, q));
+      const double d = av - bn(u, q);
       r2[u] = fma(wq * d, d, r2[u]);
     }
   }
@@ -755,6 +774,194 @@ __device__ __forceinline__ void r2xu_f64(const GA &a, const GB &b, const Weights
   }
 }
 
+// First column of wavefront w's block b: every other round of blocks is dealt in reverse,
+// as the work of a block grows with its column (B is triangular).
+__device__ __forceinline__ int rp_col(int b, int w) {
+  return 16 * (kRpWaves * b + ((b & 1) ? kRpWaves - 1 - w : w));
+}
+
+template <int NBW>
+__global__ __launch_bounds__(kRpThreads, NBW <= 2 ? 4 : 2) void refine_block(const RArgs a,
+                                                                             const Weights64 w,
+                                                                             const int no) {
+  extern __shared__ double rp_lds[];
+  const int nn = w.n_num, ni = a.R - nn;
+  double *Ks = rp_lds;                              // [32][kRpStride] kernel values
+  double *mred = Ks + kRpRows * kRpStride;          // [kRpSets][32] partial mu
+  double *sred = mred + kRpSets * kRpRows;          // [kRpWaves][32] partial row norms
+  double *cn2 = sred + kRpWaves * kRpRows;          // [2][n_num][32] candidates' numeric codes
+  double *on = cn2 + 2 * nn * kRpRows;              // [n_num][no] observations'
+  uint32_t *ci2 = reinterpret_cast<uint32_t *>(on + nn * no);  // [2][n_int][32] other words
+  uint32_t *oi = ci2 + 2 * ni * kRpRows;            // [n_int][no]
+  const int count = *a.count;
+  if (count <= kRefineBlockMin) return;
+  const int nf = a.n_f, R = a.R;
+  const int nitems = (count + kRpRows - 1) / kRpRows;
+  const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cand = tid & (kRpRows - 1), os = tid / kRpRows;
+
+  constexpr bool kEarly = NBW < kRpMaxBlocks;  // (not beside that many accumulators: spills)
+  const bool resident = kEarly && no >= nf;  // every observation's codes stay in LDS
+  auto stage_obs = [&](int i0, int cnt) {  // codes of observations i0 .. (clamped past n_f)
+    for (int e = tid; e < R * cnt; e += kRpThreads) {
+      const int i = e / R, q = e - i * R;
+      const uint32_t v = a.obs[(int64_t)min(i0 + i, nf - 1) * R + q];
+      if (q < nn) on[q * no + i] = (double)__uint_as_float(v);
+      else oi[(q - nn) * no + i] = v;
+    }
+  };
+  auto stage_cand = [&](int item, int buf) {  // the codes of an item's candidates
+    const int base = item * kRpRows, nc = min(kRpRows, count - base);
+    for (int e = tid; e < R * kRpRows; e += kRpThreads) {
+      const int q = e / kRpRows, c = e - q * kRpRows;
+      const uint32_t v = a.cand[(int64_t)q * a.ldc + a.list[base + min(c, nc - 1)]];
+      if (q < nn) cn2[(buf * nn + q) * kRpRows + c] = (double)__uint_as_float(v);
+      else ci2[(buf * ni + q - nn) * kRpRows + c] = v;
+    }
+  };
+  if (resident) stage_obs(0, no);
+  if (kEarly && (int)blockIdx.x < nitems) stage_cand(blockIdx.x, 0);
+  int buf = 0;
+  for (int item = blockIdx.x; item < nitems; item += gridDim.x, buf ^= 1) {
+    const int base = item * kRpRows, nc = min(kRpRows, count - base);
+    const int nchunks = (nf + kRpK - 1) / kRpK;
+    const double *cn = cn2 + buf * nn * kRpRows;
+    const uint32_t *ci = ci2 + buf * ni * kRpRows;
+    if (!resident) stage_obs(0, kRpK);
+    if (!kEarly) stage_cand(item, buf);
+    __syncthreads();  // the codes are there; the previous item's sums are no longer read
+    doublex4 acc[NBW][2];
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[b][r] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double mu = 0.0;
+    for (int k = 0; k < nchunks; ++k) {
+      const int k0 = k * kRpK;
+      {  // kernel values: this thread's candidate against observations k0 + os + 16 u
+        double r2[kRpObs];
+        const int oo = (resident ? k0 : 0) + os;
+        r2xu_f64<kRpObs>([&](int q) { return cn[q * kRpRows + cand]; },
+                         [&](int u, int q) { return on[q * no + oo + kRpSets * u]; },
+                         [&](int q) { return ci[(q - nn) * kRpRows + cand]; },
+                         [&](int u, int q) { return oi[(q - nn) * no + oo + kRpSets * u]; }, w, r2);
+#pragma unroll
+        for (int u = 0; u < kRpObs; ++u) {
+          const int i = k0 + os + kRpSets * u;
+          const double kv = i < nf ? matern52_f64(r2[u], a.sv) : 0.0;
+          Ks[cand * kRpStride + os + kRpSets * u] = kv;
+          mu = fma(kv, a.alpha[min(i, nf - 1)], mu);
+        }
+      }
+      __syncthreads();
+      // V[16 r + row][c] += sum_kk K[16 r + row][kk] B[k0 + kk][c]: lane supplies
+      // K[row l & 15][kk l >> 4] and B[kk l >> 4][col l & 15] per 4-deep step
+#pragma nounroll
+      for (int s0 = 0; s0 < kRpK && k0 + s0 < nf; s0 += 16) {
+        double av[2][4];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) av[r][s] = Ks[(16 * r + fr) * kRpStride + s0 + 4 * s + fg];
+        constexpr int kAhead = NBW < 4 ? NBW : 4;  // column blocks whose loads are in flight
+#pragma unroll
+        for (int h = 0; h < NBW; h += kAhead) {
+          double bv[kAhead][4];
+#pragma unroll
+          for (int b = 0; b < kAhead; ++b) {
+            const int cb = rp_col(h + b, wv);
+            if (cb + 15 >= k0 + s0 && cb < nf) {  // wave-uniform
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                bv[b][s] = a.B64[(int64_t)min(k0 + s0 + 4 * s + fg, nf - 1) * a.ldb + min(cb + fr, nf - 1)];
+            }
+          }
+#pragma unroll
+          for (int b = 0; b < kAhead; ++b) {
+            const int cb = rp_col(h + b, wv);
+            if (cb + 15 >= k0 + s0 && cb < nf) {
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+                  acc[h + b][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r][s], bv[b][s], acc[h + b][r], 0, 0, 0);
+            }
+          }
+        }
+      }
+      if (!resident && k + 1 < nchunks) stage_obs((k + 1) * kRpK, kRpK);
+      // the next item's candidates, beside the other wavefronts' products
+      if (kEarly && k == 0 && item + (int)gridDim.x < nitems) stage_cand(item + gridDim.x, buf ^ 1);
+      __syncthreads();
+    }
+    // squared row norms: lane holds rows 16 r + (l >> 4) + 4 v of column l & 15 of its blocks
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      double sq[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = 0.0;
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) {
+          const bool in = rp_col(b, wv) + fr < nf;
+          s = in ? fma(acc[b][r][v], acc[b][r][v], s) : s;
+        }
+        sq[v] = s;
+      }
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sq[v] += __shfl_xor(sq[v], off);
+      if (fr == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sred[wv * kRpRows + 16 * r + fg + 4 * v] = sq[v];
+      }
+    }
+    mred[os * kRpRows + cand] = mu;
+    __syncthreads();
+    if (tid < nc) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < kRpWaves; ++q) s += sred[q * kRpRows + tid];
+      a.part64[base + tid] = s;
+      double m = 0.0;
+#pragma unroll
+      for (int q = 0; q < kRpSets; ++q) m += mred[q * kRpRows + tid];
+      a.mu64[base + tid] = m;
+    }
+  }
+}
+
+// The block path for n_f > kRpMaxCols, where B no longer fits an XCD's L2 and twice the
+// candidates per read of it are worth more (n_f = 1500, 65,536 candidates: 5.0 ms against
+// 5.4): a work item is a group of 64 flagged candidates and a tile of
+// 256 columns of B = L_f^-T, run by a persistent workgroup of 16 wavefronts. Per
+// 16-observation chunk, eight staging wavefronts compute the 64 x 16 fp64 kernel values
+// and load the 16 x 256 block of B into one LDS buffer while eight compute wavefronts
+// accumulate V += K B on fp64 MFMA from the other buffer (each 16 candidates x 128
+// columns; column blocks wholly left of the chunk, or wholly past n_f, are skipped, as B
+// is upper triangular); one barrier per chunk swaps the buffers. Two wavefronts of each
+// role share a SIMD, so that one's latency is covered by the other's work. The
+// candidates' codes are staged in LDS per item, alpha and the weights once; a staging
+// wavefront reads its observations' codes through the scalar cache (they are the same
+// for all its lanes). The tile's squared row norms go to part64; the last tile (whose
+// k-range covers all n_f observations) also forms mu = K alpha. refine_block_finish sums
+// the tiles in order.
+constexpr int kRbK = 16;                     // observations per chunk
+constexpr int kRbBS = kRefineBlockCols + 8;  // LDS row stride of the B block (doubles)
+constexpr int kRbKS = kRbK + 1;              // LDS row stride of the kernel block
+constexpr int kRbRoleWaves = 8;              // compute wavefronts = staging wavefronts
+constexpr int kRbWaves = 2 * kRbRoleWaves;
+constexpr int kRbObs = kRbK / kRbRoleWaves;  // observations per staging lane and chunk
+constexpr int kRbCols = kRefineBlockCols / 2;  // columns per compute wavefront
+constexpr int kRbKsD = kRefineBlockRows * kRbKS, kRbBsD = kRbK * kRbBS;  // doubles per buffer
+constexpr size_t kRbFixedBytes =
+    sizeof(double) * (2 * kRbKsD + 2 * kRbBsD + 4 * kRefineBlockRows + kRefineBlockRows);
+constexpr size_t kRbMaxLds = 160 * 1024 - 2048;  // dynamic LDS (the weights take the rest)
+static_assert(sizeof(Weights64) <= 2048, "weights in LDS");
+static_assert(kRbK % kRbRoleWaves == 0 && kRbRoleWaves == 8, "roles");
+
 __device__ __forceinline__ void barrier_rb() {
   __asm__ volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
@@ -762,7 +969,7 @@ __device__ __forceinline__ void barrier_rb() {
 }
 __device__ __forceinline__ void wait_lds_rb() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0)
 
-__global__ __launch_bounds__(64 * kRbWaves, 1) void refine_block(const RArgs a, const Weights64 w) {
+__global__ __launch_bounds__(64 * kRbWaves, 1) void refine_block_tall(const RArgs a, const Weights64 w) {
   extern __shared__ double rb_lds[];
   __shared__ Weights64 wl;  // the weights, read in the kernel values' loops, from LDS
   double *Ks = rb_lds;                          // [2][64][kRbKS]
@@ -825,8 +1032,11 @@ __global__ __launch_bounds__(64 * kRbWaves, 1) void refine_block(const RArgs a, 
         for (int u = 0; u < kRbObs; ++u)
           orow[u] = (const cu32 *)(a.obs + (int64_t)min(i0 + u, kend - 1) * R);
         double r2[kRbObs];
-        r2xu_f64<kRbObs>([&](int q) { return cw[q * kRefineBlockRows + lane]; },
-                         [&](int u, int q) { return orow[u][q]; }, wl, r2);
+        r2xu_f64<kRbObs>(
+            [&](int q) { return (double)__uint_as_float(cw[q * kRefineBlockRows + lane]); },
+            [&](int u, int q) { return (double)__uint_as_float(orow[u][q]); },
+            [&](int q) { return cw[q * kRefineBlockRows + lane]; },
+            [&](int u, int q) { return orow[u][q]; }, wl, r2);
 #pragma unroll
         for (int u = 0; u < kRbObs; ++u)
           kb[lane * kRbKS + kRbObs * sw + u] =
@@ -923,10 +1133,10 @@ __global__ __launch_bounds__(64 * kRbWaves, 1) void refine_block(const RArgs a, 
   }
 }
 
-__global__ __launch_bounds__(256) void refine_block_finish(const RArgs a, const float *pwork) {
+__global__ __launch_bounds__(256) void refine_block_finish(const RArgs a, int nct,
+                                                           const float *pwork) {
   const int count = *a.count;
   if (count <= kRefineBlockMin) return;
-  const int nct = (a.n_f + kRefineBlockCols - 1) / kRefineBlockCols;
   for (int q = blockIdx.x * 256 + threadIdx.x; q < count; q += gridDim.x * 256) {
     double ssq = 0.0;
     for (int ct = 0; ct < nct; ++ct) ssq += a.part64[(int64_t)ct * a.cap + q];
@@ -1117,26 +1327,60 @@ hipError_t launch_refine_cb(const RArgs &a, const Weights64 &w, const float *pwo
   return hipGetLastError();
 }
 
-hipError_t launch_refine_block(const RArgs &a, const Weights64 &w, int cus, hipStream_t s) {
-  // (its kernel returns at once unless more than kRefineBlockMin are flagged)
-  if (a.cap <= kRefineBlockMin) return hipSuccess;
-  if (!a.part64 || !a.mu64 || cus < 1) return hipErrorInvalidValue;
-  const int nct = (a.n_f + kRefineBlockCols - 1) / kRefineBlockCols;
-  const int64_t items = (a.cap + kRefineBlockRows - 1) / kRefineBlockRows * nct;
+// Column tiles of the block path: one up to kRpMaxCols columns, then the tall form's.
+int refine_block_tiles(int n_f) {
+  return n_f <= kRpMaxCols ? 1 : (n_f + kRefineBlockCols - 1) / kRefineBlockCols;
+}
+
+hipError_t launch_refine_block_tall(const RArgs &a, const Weights64 &w, int cus, hipStream_t s) {
+  const int64_t items = (a.cap + kRefineBlockRows - 1) / kRefineBlockRows * refine_block_tiles(a.n_f);
   const size_t lds = kRbFixedBytes + sizeof(uint32_t) * (size_t)a.R * kRefineBlockRows +
                      sizeof(double) * a.n_f;
   if (lds > kRbMaxLds) return hipErrorInvalidValue;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_block),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_block_tall),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRbMaxLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   // persistent: one workgroup per compute unit the stream can use
-  hipLaunchKernelGGL(refine_block, dim3((unsigned)std::min<int64_t>(items, cus)),
+  hipLaunchKernelGGL(refine_block_tall, dim3((unsigned)std::min<int64_t>(items, cus)),
                      dim3(64 * kRbWaves), lds, s, a, w);
   return hipGetLastError();
+}
+
+template <int NBW>
+hipError_t launch_refine_block_n(const RArgs &a, const Weights64 &w, int64_t items, size_t lds,
+                                 int no, int cus, hipStream_t s) {
+  static bool attr_set = false;  // per instantiation
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_block<NBW>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRpMaxLds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  // persistent: the workgroups that the stream's compute units can hold (registers allow two
+  // of them per unit for narrow tiles)
+  hipLaunchKernelGGL(refine_block<NBW>, dim3((unsigned)std::min<int64_t>(items, (NBW <= 2 ? 2 : 1) * (int64_t)cus)),
+                     dim3(kRpThreads), lds, s, a, w, no);
+  return hipGetLastError();
+}
+
+hipError_t launch_refine_block(const RArgs &a, const Weights64 &w, int cus, hipStream_t s) {
+  // (its kernel returns at once unless more than kRefineBlockMin are flagged)
+  if (a.cap <= kRefineBlockMin) return hipSuccess;
+  if (!a.part64 || !a.mu64 || cus < 1 || a.n_f < 1 || a.R < w.n_num) return hipErrorInvalidValue;
+  if (a.n_f > kRpMaxCols) return launch_refine_block_tall(a, w, cus, s);
+  const int64_t items = (a.cap + kRpRows - 1) / kRpRows;
+  const int no = rp_obs(a.n_f, w.n_num, a.R - w.n_num);
+  const size_t lds = rp_lds_bytes(w.n_num, a.R - w.n_num, no);
+  if (lds > kRpMaxLds) return hipErrorInvalidValue;
+  switch (rp_blocks(a.n_f)) {
+    case 2: return launch_refine_block_n<2>(a, w, items, lds, no, cus, s);
+    case 4: return launch_refine_block_n<4>(a, w, items, lds, no, cus, s);
+    default: return launch_refine_block_n<kRpMaxBlocks>(a, w, items, lds, no, cus, s);
+  }
 }
 
 hipError_t launch_refine_rest(const RArgs &a, const Weights64 &w, const float *pwork, int grid,
@@ -1157,7 +1401,7 @@ hipError_t launch_refine_rest(const RArgs &a, const Weights64 &w, const float *p
   if (a.cap > kRefineBlockMin) {
     if (!a.part64 || !a.mu64) return hipErrorInvalidValue;
     hipLaunchKernelGGL(refine_block_finish, dim3((unsigned)std::min<int64_t>((a.cap + 255) / 256, 1024)),
-                       dim3(256), 0, s, a, pwork);
+                       dim3(256), 0, s, a, refine_block_tiles(a.n_f), pwork);
   }
   return hipGetLastError();
 }

@@ -212,3 +212,29 @@ def test_log_posterior_shapes(d, n, count):
         rv, rg = gh.log_posterior(T, yf, theta[b], (1.5, 1.0), 1e-6)
         assert abs(out["value"][b].item() - rv) <= 1e-10 * max(abs(rv), 1.0)
         assert np.abs(out["grad"][b].cpu().numpy() - rg).max() <= 1e-9 * max(np.abs(rg).max(), 1.0)
+
+
+@pytest.mark.parametrize("n", [3, 31, 32, 63, 65, 200, 256, 257, 513, 1024, 1025])
+def test_refine_block_sizes(n):
+    """Every candidate recomputed in fp64 in groups (more than 4096 flagged) gives what the
+    small-count path gives, at the edges of its observation chunks, column blocks and forms,
+    with a ragged last group. Both are fp64 sums rounded to fp32 (mu, sigma, EI); the sum of
+    squares is 1 - sigma^2, so sigma's bound grows as it cancels: n eps / sigma^2 with the
+    fp32 rounding on top."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    M = 4096 + 33
+    w = make_workload("C1", M, n=n)
+    space, model = _fit(w)
+    gp.debug_set_refine(model, float("inf"), -1.0)
+    C = gp.to_device_columns(space, w.C)
+    big = gp.score(model, C)
+    parts = [gp.score(model, [c[a:a + 100].contiguous() for c in C]) for a in (0, 2000, M - 100)]
+    for a, p in zip((0, 2000, M - 100), parts):
+        for k in ("mu", "sigma", "ei"):
+            x, y = big[k][a:a + 100].double(), p[k].double()
+            tol = 4e-7 * torch.maximum(y.abs(), torch.full_like(y, 1e-3 if k == "mu" else 0.0))
+            if k != "mu":  # eps n cond of the cancellation, in units of sigma
+                tol = tol + 1e-14 * n / p["sigma"].double().clamp(min=1e-3)
+            assert bool(((x - y).abs() <= tol).all()), (k, a, float((x - y).abs().max()))
