@@ -238,3 +238,19 @@ def test_refine_block_sizes(n):
             if k != "mu":  # eps n cond of the cancellation, in units of sigma
                 tol = tol + 1e-14 * n / p["sigma"].double().clamp(min=1e-3)
             assert bool(((x - y).abs() <= tol).all()), (k, a, float((x - y).abs().max()))
+
+
+@pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 1023, 1025, 32767, 32768, 32769])
+def test_argmax_sizes(M):
+    """The arg-max (lowest index on ties) on both sides of its one-workgroup form: free, and
+    with all but a few masked off, where most values tie at zero."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload("C1", 36864, n=20)
+    space, model = _fit(w)
+    C = [c[:M].contiguous() for c in gp.to_device_columns(space, w.C)]
+    for mask in (None, torch.zeros(M, dtype=torch.uint8, device="cuda"),
+                 (torch.arange(M, device="cuda") % 997 == 996).to(torch.uint8)):
+        out = gp.score(model, C, mask=mask, want_argmax=True)
+        assert int(out["argmax"][0]) == int(np.argmax(out["acq"].cpu().numpy()))
