@@ -395,7 +395,7 @@ def time_forest(gp, space, X, feas, Cc, n_trees, reps=3):
     return {"trees": n_trees, "max_depth": 16, "nodes": nodes, "fit_ms": fit_ms,
             "predict_M": M, "predict_ms": pr_ms, "predict_candidates_per_s": M / (pr_ms * 1e-3),
             "tree_walks_per_s": M * n_trees / (pr_ms * 1e-3), "mean_p": float(p.mean()),
-            "bound": "latency of the dependent node loads (L2-resident trees)"}
+            "bound": "latency of the dependent node loads (trees in LDS)"}
 
 
 def time_other_workloads(gp, names, steps=5, warmup=2):
@@ -466,7 +466,7 @@ def time_cot(gp, M, reps=5):
             "M": M, "sample_ms": s_ms, "member_ms": m_ms,
             "sample_configs_per_s": M / (s_ms * 1e-3), "member_configs_per_s": M / (m_ms * 1e-3),
             "sample_gbs": 48 * M / (s_ms * 1e-3) / 1e9, "member_gbs": 49 * M / (m_ms * 1e-3) / 1e9,
-            "bound": "hbm (draw); latency of the binary search (membership)"}
+            "bound": "hbm (draw); one random line per lookup (membership)"}
 
 
 def keep_tiles(model, fused):

@@ -440,7 +440,7 @@ hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const uint
 // Hidden constraints (Sec. 4.2): a classification forest of CART trees on bootstrap
 // samples of the observations; features are REAL/INT values, ORD/CAT indices and PERM
 // positions (one per item), stored as fp64.
-constexpr int kForestMaxF = 120;     // features (prediction keeps 64 x F fp64 in LDS)
+constexpr int kForestMaxF = 120;     // features (prediction keeps a wavefront's 64 x F 16-bit ranks in LDS)
 constexpr int kForestMaxMtry = 16;   // features tried per node (floor(sqrt(F)))
 struct ForestDesc {
   int32_t d, F, n, n_trees, max_depth, min_split, mtry, cap;  // cap: nodes per tree (2n)
