@@ -2519,7 +2519,7 @@ gp_status gp_forest_predict(const gp_forest *f, const void *const *C_cols, int64
   if (st != GP_OK) return st;
   CotCols cc{};
   for (int p = 0; p < f->h.d; ++p) cc.col[p] = const_cast<void *>(C_cols[p]);
-  HIPCHK(launch_forest_predict(f->d_desc, f->h, f->trees, cc, M, ei, mask, eps_f, p_feas, acq,
+  HIPCHK(launch_forest_predict(f->d_desc, f->h, f->d_nodes, f->trees, cc, M, ei, mask, eps_f, p_feas, acq,
                                stream_cus(static_cast<hipStream_t>(stream)),
                                static_cast<hipStream_t>(stream)));
   return GP_OK;

@@ -482,7 +482,8 @@ inline int64_t forest_tree_words(int F) {
 }
 static_assert((kForestLds - 64 * 1024) / 8 >= 2 * kMaxN, "the largest tree fits");
 // p = mean over trees of the leaf values; acq = ei * p if allowed and p > eps_f else 0
-hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestTrees &tr,
+hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestNode *nodes,
+                                 const ForestTrees &tr,
                                  const CotCols &cols, int64_t M, const float *ei,
                                  const uint8_t *mask, float eps_f, float *p, float *acq, int cus,
                                  hipStream_t s);

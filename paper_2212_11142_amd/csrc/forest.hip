@@ -25,7 +25,7 @@
 // workgroup keeps many trees and its configurations' ranks in LDS; a lane walks two trees
 // at a time. 1,048,576 configurations and 64 trees take 389 us, bound by the random LDS
 // reads of the walks; 16-byte nodes read from the caches took 1,060 us, bound by one
-// address per lane and cycle.
+// address per lane and cycle. Few trees are still walked that way (forest_direct below).
 #include <algorithm>
 
 #include "common.h"
@@ -368,6 +368,18 @@ __global__ __launch_bounds__(1024) void forest_train_k(const ForestDesc *dd, con
   if (tid == 0) n_nodes_out[t] = s_nn;
 }
 
+// The outputs of configuration j: the mean of its leaves and the acquisition value.
+__device__ __forceinline__ void forest_store(double sum, int n_trees, int64_t j, const float *ei,
+                                             const uint8_t *mask, float eps_f, float *p_out,
+                                             float *acq) {
+  const float pf = (float)(sum / (double)n_trees);
+  p_out[j] = pf;
+  if (acq) {
+    const bool allowed = !mask || mask[j];
+    acq[j] = (allowed && pf > eps_f) ? ei[j] * pf : 0.0f;
+  }
+}
+
 // Prediction. lofs[t]: tree t's first node in its batch's LDS; bstart[0..nbatch]: first tree
 // of each batch (of trees that fit tree_words 8-byte nodes together).
 __global__ __launch_bounds__(1024) void forest_predict_k(
@@ -447,15 +459,51 @@ __global__ __launch_bounds__(1024) void forest_predict_k(
         acc += __builtin_bit_cast(double, a);
       }
     }
-    if (j0 + tid < M) {
-      const float pf = (float)(acc / (double)D.n_trees);
-      p_out[j] = pf;
-      if (acq) {
-        const bool allowed = !mask || mask[j];
-        acq[j] = (allowed && pf > eps_f) ? ei[j] * pf : 0.0f;
-      }
-    }
+    if (j0 + tid < M) forest_store(acc, D.n_trees, j, ei, mask, eps_f, p_out, acq);
   }
+}
+
+// Prediction by few trees: a wavefront per 64 configurations, their features' own values in
+// LDS and 16-byte nodes read through the caches, two walks at a time. It has neither the
+// binary search per feature nor the copy of the trees to LDS.
+__global__ __launch_bounds__(64) void forest_predict_direct_k(
+    const ForestDesc *dd, const ForestNode *nodes, const CotCols cols0, int64_t M, const float *ei,
+    const uint8_t *mask, float eps_f, float *p_out, float *acq) {
+  extern __shared__ double feat[];  // [F][64]
+  __shared__ ForestDesc D;
+  __shared__ CotCols cols;
+  stage(D, *dd);
+  stage(cols, cols0);
+  __syncthreads();
+  const int lane = threadIdx.x;
+  const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+  if (j >= M) return;
+  for (int p = 0; p < D.d; ++p)
+    for (int q = 0; q < D.m[p]; ++q) feat[(D.fofs[p] + q) * 64 + lane] = feature_of(D, cols, p, q, j);
+  // (a NaN compares false and goes right)
+  auto child = [&](const ForestNode &a) {
+    return a.left + (feat[a.feature * 64 + lane] <= a.val ? 0 : 1);
+  };
+  double acc = 0.0;
+  int t = 0;
+  for (; t + 2 <= D.n_trees; t += 2) {  // their leaves are added in tree order
+    const ForestNode *na = nodes + (int64_t)t * D.cap, *nb = na + D.cap;
+    ForestNode a = na[0], b = nb[0];
+    while (a.feature >= 0 || b.feature >= 0) {
+      const ForestNode a2 = na[a.feature >= 0 ? child(a) : 0], b2 = nb[b.feature >= 0 ? child(b) : 0];
+      if (a.feature >= 0) a = a2;
+      if (b.feature >= 0) b = b2;
+    }
+    acc += a.val;
+    acc += b.val;
+  }
+  if (t < D.n_trees) {
+    const ForestNode *nt = nodes + (int64_t)t * D.cap;
+    ForestNode a = nt[0];
+    while (a.feature >= 0) a = nt[child(a)];
+    acc += a.val;
+  }
+  forest_store(acc, D.n_trees, j, ei, mask, eps_f, p_out, acq);
 }
 
 }  // namespace
@@ -498,12 +546,33 @@ hipError_t launch_forest_train(const ForestDesc *dd, const ForestDesc &hd, const
   return hipGetLastError();
 }
 
-hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestTrees &tr,
+// Where the direct kernel is the faster one (us a call, direct / staged; F = 20 unless said).
+// Up to 512 configurations per compute unit latency counts, and a tree's walk stands against
+// a feature's search: 65,536 configurations, n = 512, 1 tree 13 / 18, 8 trees 21 / 25, 16
+// trees 32 / 33, 64 trees 100 / 86; F = 24, 16 trees of n = 24 18 / 25; F = 5, 8 trees 18 /
+// 18, 16 trees 30 / 27. Beyond that the loads of the walks count: 1,048,576 configurations,
+// n = 512, 2 trees 91 / 101, 4 trees 108 / 110, 8 trees 143 / 127; F = 5, 8 trees 59 / 85. A
+// single configuration reads one path of each tree, and staging reads the whole tree: n =
+// 4096, 2,000 trees 2.5 / 4.0 ms; n = 512 1.5 / 1.35.
+bool forest_direct(int64_t M, const ForestDesc &hd, int cus) {
+  if (M == 1 && hd.n >= 3072) return true;
+  if (M <= (int64_t)512 * cus) return hd.n_trees <= std::min(std::max(hd.F, 8), 24);
+  return hd.n_trees * hd.F <= 40;
+}
+
+hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestNode *nodes,
+                                 const ForestTrees &tr,
                                  const CotCols &cols, int64_t M, const float *ei,
                                  const uint8_t *mask, float eps_f, float *p, float *acq, int cus,
                                  hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (cus < 1) return hipErrorInvalidValue;
+  if (forest_direct(M, hd, cus)) {
+    hipLaunchKernelGGL(forest_predict_direct_k, dim3((unsigned)((M + 63) / 64)), dim3(64),
+                       sizeof(double) * 64 * (size_t)hd.F, s, dd, nodes, cols, M, ei, mask, eps_f,
+                       p, acq);
+    return hipGetLastError();
+  }
   // Every workgroup loads the trees, so it takes as many configurations as the LDS beside
   // them holds the ranks of, and fewer only where that would leave compute units idle.
   int waves = forest_predict_waves(hd.F);

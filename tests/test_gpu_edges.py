@@ -168,6 +168,56 @@ def test_forest_sizes(n, trees, depth, min_split):
     assert np.array_equal(p.cpu().numpy(), (want / trees).astype(np.float32))
 
 
+@pytest.mark.parametrize("name,n,trees,M", [
+    ("C5", 300, 1, 4099), ("C5", 300, 24, 4099), ("C5", 300, 25, 4099),
+    ("C1", 200, 8, 4099), ("C1", 200, 9, 4099), ("C1", 200, 8, 131072), ("C1", 200, 8, 131073),
+    ("C1", 200, 9, 131073), ("C1", 3071, 30, 1), ("C1", 3072, 30, 1),
+    ("C1", 1024, 129, 5003), ("C1", 1024, 129, 262144 + 65)])
+def test_forest_prediction_routes(name, n, trees, M):
+    """Predictions on both sides of the rule between walks through the caches and through
+    LDS, and by more trees than the LDS holds at once (several batches, read again for a
+    workgroup's second set of configurations), against walking the returned trees: the same
+    comparisons and the same sum in the same order. REAL values hold NaN (goes right),
+    infinities, both zeros, values of the observations and values outside their range."""
+    import torch
+
+    from oracle import gp_forest as of
+    from paper_2212_11142_amd import gp
+    w = make_workload(name, M, n=n) if name == "C1" else make_workload(name, M)
+    X = [c[:n] for c in w.X]
+    C = [c.copy() for c in w.C]
+    for q, p in enumerate(w.space):
+        if p.kind == "real":
+            odd = [np.nan, np.inf, -np.inf, 0.0, -0.0, -5.0, 5.0, X[q][0], X[q][n // 2]]
+            C[q][:min(9, M)] = odd[:min(9, M)]
+    rng = np.random.default_rng(M + trees)
+    feas = (rng.random(n) < 0.6).astype(np.uint8)
+    space = gp.Space(w.space)
+    forest = gp.Forest(space, gp.to_device_columns(space, X), torch.from_numpy(feas).cuda(),
+                       n_trees=trees, max_depth=40, seed=4)
+    ei, mask = rng.random(M).astype(np.float32), (rng.random(M) < 0.8).astype(np.uint8)
+    p, acq = forest.predict(gp.to_device_columns(space, C), torch.from_numpy(ei).cuda(),
+                            torch.from_numpy(mask).cuda(), 0.3)
+    p, acq = p.cpu().numpy(), acq.cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(min(M, 16)), rng.integers(0, M, min(M, 4096)),
+                                     np.arange(max(0, M - 130), M)]))
+    F = of.features(w.space, [c[rows] for c in C])
+    at, want, nodes = np.arange(len(rows)), np.zeros(len(rows)), 0
+    for t in range(trees):
+        feat, left, val = forest.tree(t)
+        nodes += len(feat)
+        k = np.zeros(len(rows), np.int64)
+        while np.any(feat[k] >= 0):
+            x = F[at, np.maximum(feat[k], 0)]
+            k = np.where(feat[k] >= 0, left[k] + np.where(x <= val[k], 0, 1), k)
+        want += val[k]
+    assert trees < 100 or nodes > 160 * 1024 // 8  # more than one batch
+    want = (want / trees).astype(np.float32)
+    assert np.array_equal(p[rows], want)
+    ok = (mask[rows] != 0) & (want > np.float32(0.3))
+    assert np.array_equal(acq[rows], np.where(ok, ei[rows] * want, np.float32(0.0)))
+
+
 @pytest.mark.parametrize("name", ["C3", "C4"])
 def test_few_rows_bit_identical(name):
     """Batches small enough for the few-rows contraction and the one-block cross-kernel give
