@@ -78,6 +78,13 @@ def test_start_selection(M, k):
     assert np.array_equal(out["acq"].cpu().numpy(), acq[want])
 
 
+@pytest.mark.parametrize("k", [1, 64])
+@pytest.mark.parametrize("M", [63, 127, 129, 16383, 16384, 16385])
+def test_start_selection_blocks(M, k):
+    """The same where the number of blocks and the elements of a block change."""
+    test_start_selection(M, k)
+
+
 @pytest.mark.parametrize("sizes", [[1], [2], [4], [5], [6], [7], [39], [41], [300000],
                                    [1, 5, 5000, 200000]])
 def test_chain_membership_tables(sizes):
