@@ -21,6 +21,7 @@
 #include <cstddef>
 
 #include "baco_gp.h"
+#include "lds_limit.h"
 
 namespace bgp {
 

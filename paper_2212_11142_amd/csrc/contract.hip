@@ -1347,13 +1347,9 @@ int refine_candidates_per_block(int n_f) {
 template <int CB>
 hipError_t launch_refine_cb(const RArgs &a, const Weights64 &w, const float *pwork, int grid,
                             hipStream_t s) {
-  static bool attr_set = false;  // per instantiation
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_kernel<CB>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kRefineLds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;  // per instantiation
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&refine_kernel<CB>), kRefineLds);
+  if (e != hipSuccess) return e;
   const size_t lds = (size_t)CB * a.n_f * sizeof(double);
   hipLaunchKernelGGL(refine_kernel<CB>, dim3(grid), dim3(256), lds, s, a, w, pwork);
   return hipGetLastError();
@@ -1369,13 +1365,9 @@ hipError_t launch_refine_block_tall(const RArgs &a, const Weights64 &w, int cus,
   const size_t lds = kRbFixedBytes + sizeof(uint32_t) * (size_t)a.R * kRefineBlockRows +
                      sizeof(double) * a.n_f;
   if (lds > kRbMaxLds) return hipErrorInvalidValue;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_block_tall),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRbMaxLds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&refine_block_tall), (int)kRbMaxLds);
+  if (e != hipSuccess) return e;
   // persistent: one workgroup per compute unit the stream can use
   hipLaunchKernelGGL(refine_block_tall, dim3((unsigned)std::min<int64_t>(items, cus)),
                      dim3(64 * kRbWaves), lds, s, a, w);
@@ -1385,13 +1377,9 @@ hipError_t launch_refine_block_tall(const RArgs &a, const Weights64 &w, int cus,
 template <int NBW>
 hipError_t launch_refine_block_n(const RArgs &a, const Weights64 &w, int64_t items, size_t lds,
                                  int no, int cus, hipStream_t s) {
-  static bool attr_set = false;  // per instantiation
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&refine_block<NBW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRpMaxLds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;  // per instantiation
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&refine_block<NBW>), (int)kRpMaxLds);
+  if (e != hipSuccess) return e;
   // persistent: the workgroups that the stream's compute units can hold (registers allow two
   // of them per unit for narrow tiles)
   hipLaunchKernelGGL(refine_block<NBW>, dim3((unsigned)std::min<int64_t>(items, (NBW <= 2 ? 2 : 1) * (int64_t)cus)),

@@ -534,13 +534,9 @@ hipError_t launch_forest_train(const ForestDesc *dd, const ForestDesc &hd, const
   const size_t lds = sizeof(uint32_t) * (size_t)waves * bins + 2 * sizeof(uint16_t) * (size_t)((hd.n + 1) & ~1);
   constexpr size_t kMaxLds = 158 * 1024;
   if (lds > kMaxLds) return hipErrorInvalidValue;
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&forest_train_k),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&forest_train_k), (int)kMaxLds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(forest_train_k, dim3((unsigned)hd.n_trees), dim3(64 * waves), lds, s, dd, rank,
                      val, nd, y, nodes, pack, aux, n_nodes, bins);
   return hipGetLastError();
@@ -579,13 +575,9 @@ hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, con
   while (waves > 4 && M < (int64_t)64 * waves * cus) waves >>= 1;
   const size_t lds = sizeof(uint64_t) * tr.tree_words + (size_t)waves * hd.F * 64 * sizeof(uint16_t);
   if (lds > kForestLds) return hipErrorInvalidValue;
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&forest_predict_k),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kForestLds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&forest_predict_k), (int)kForestLds);
+  if (e != hipSuccess) return e;
   const int64_t blocks = std::min<int64_t>((M + 64 * waves - 1) / (64 * waves), cus);
   hipLaunchKernelGGL(forest_predict_k, dim3((unsigned)blocks), dim3(64 * waves), lds, s, dd, tr.pack,
                      tr.n_nodes, tr.lofs, tr.bstart, tr.nbatch, (int)tr.tree_words, tr.val, tr.nd,

@@ -542,14 +542,10 @@ hipError_t launch_ls_topk(const float *acq, int64_t M, int k, int64_t *part, flo
   // ranges of 64 / 256 / 1024: 5,000 elements, k = 1 8.9 / 12.6 / 25, k = 64 29 / 29 / 41;
   // 16,384, k = 8 11 / 13 / 25; one reduction per pick, as it was before: k = 1 8.6, k = 64 813).
   const int parts = (int)std::min<int64_t>((M + kTopkLeast - 1) / kTopkLeast, kTopkParts);
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ls_topk_final),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             kTopkParts * kLsMaxStarts * (int)sizeof(uint64_t));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.set(reinterpret_cast<const void *>(&ls_topk_final),
+                                 kTopkParts * kLsMaxStarts * (int)sizeof(uint64_t));
+  if (e != hipSuccess) return e;
   uint64_t *lists = reinterpret_cast<uint64_t *>(part);
   hipLaunchKernelGGL(ls_topk_partial, dim3(parts), dim3(256), 0, s, acq, map, M, k, lists);
   hipLaunchKernelGGL(ls_topk_final, dim3(1), dim3(1024), sizeof(uint64_t) * parts * k, s, lists,
