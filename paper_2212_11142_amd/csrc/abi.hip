@@ -557,9 +557,9 @@ hipError_t score_xkernel(const gp_model &m, const ScorePlan &P, int64_t rows, hi
   return launch_xkernel(xa, m.variant, P.xs, s, false, false);  // the epilogue sums splits
 }
 
-// The contraction over the column tiles [t0, t1) of the model.
+// The contraction over the column tiles [t0, t1) of the model (cus: s's compute units).
 hipError_t contract_tiles(const gp_model &m, const ScorePlan &P, int64_t rows, int t0, int t1,
-                          hipStream_t s) {
+                          int cus, hipStream_t s) {
   if (t1 <= t0) return hipSuccess;
   CArgs ca{};
   ca.A = P.Kstar;
@@ -572,7 +572,7 @@ hipError_t contract_tiles(const gp_model &m, const ScorePlan &P, int64_t rows, i
   ca.lin = P.fbar;
   ca.rows = rows;
   for (int t = t0; t < t1; ++t) ca.tiles[t - t0] = m.tiles[t];
-  return launch_contract(ca, s);
+  return launch_contract(ca, cus, s);
 }
 
 int stream_cus(hipStream_t s);
@@ -666,7 +666,8 @@ hipError_t score_back(const gp_model &m, const ScorePlan &P, int64_t M, int64_t 
                       const ScoreOut &o, int tile0, hipStream_t s, hipEvent_t *ev,
                       hipEvent_t value_done = nullptr) {
   if (ev && tile0 > 0) HIPRET(hipEventRecord(ev[kProfLate], s));
-  HIPRET(contract_tiles(m, P, rows, tile0, m.ntiles, s));
+  const int cus = stream_cus(s);
+  HIPRET(contract_tiles(m, P, rows, tile0, m.ntiles, cus, s));
   if (ev) HIPRET(hipEventRecord(ev[3], s));
   const EArgs ea = make_eargs(m, P, M, rows, o);
   float *pwork = o.p_feas ? o.p_feas : P.pwork;
@@ -678,7 +679,7 @@ hipError_t score_back(const gp_model &m, const ScorePlan &P, int64_t M, int64_t 
     if (ev) HIPRET(hipEventRecord(ev[kProfValEpi], s));
     HIPRET(launch_epilogue(ea, pwork, s));
     if (ev) HIPRET(hipEventRecord(ev[kProfValEpi + 1], s));
-    HIPRET(launch_refine_block(make_rargs(m, P, rows, o), m.lay.w64, stream_cus(s), s));
+    HIPRET(launch_refine_block(make_rargs(m, P, rows, o), m.lay.w64, cus, s));
     if (ev) HIPRET(hipEventRecord(ev[kProfValEpi + 2], s));
     if (ev) HIPRET(hipEventRecord(ev[kProfClsEpi], s));
   }
@@ -1235,7 +1236,7 @@ gp_status fit_impl(const gp_space *space, const void *const *X_cols, int32_t n, 
       if (pev) HIPCHK(hipEventRecord(pev[2], sv));
       if (sx != sv) HIPCHK(hipStreamWaitEvent(sv, ev_vaux, 0));  // packed B^T and f*
       if (pev) HIPCHK(hipEventRecord(pev[kProfEarly], sv));
-      HIPCHK(contract_tiles(*m, SP, rows, 0, m->n_reg_tiles, sv));
+      HIPCHK(contract_tiles(*m, SP, rows, 0, m->n_reg_tiles, stream_cus(sv), sv));
       if (pev) HIPCHK(hipEventRecord(pev[kProfEarly + 1], sv));
       HIPCHK(hipEventRecord(ev_vcon, sv));
       HIPCHK(score_value_tail(*m, SP, job->M, rows, job->o, P.fstar, sv, pev));

@@ -302,7 +302,7 @@ size_t xobs_r_words_max(int n);
 hipError_t launch_make_xobs(const uint32_t *codes, int32_t R, int32_t n, const XObsLayout &lay,
                             const double *num_scale, const double *alpha, int32_t n_f,
                             double *xa, uint32_t *xr, hipStream_t s);
-hipError_t launch_contract(const CArgs &a, hipStream_t s);
+hipError_t launch_contract(const CArgs &a, int cus, hipStream_t s);  // cus: the stream's compute units
 // pwork: float[M] receiving p_feas (the caller's p_feas output or workspace); the
 // refinement pass reads it back.
 // The value model's half of the epilogue (mu, sigma, EI of the candidates kept in fp32,

@@ -1292,12 +1292,14 @@ __global__ __launch_bounds__(256) void gather_rows_split(const _Float16 *src, in
 
 }  // namespace
 
-// contract_few while its workgroups are at most one per compute unit. Measured (us, with
-// timing events; contract_few / contract_split): 16 tiles of 128 x 128 at n = 512 10.8 /
-// 17.1, 24 at n = 1500 20 / 35, 32 at n = 128 7.1 / 9.0; 64 at n = 512 16.5 / 17.1, 64 at
-// n = 128 10.3 / 9.4, 96 at n = 1500 48 / 38.
-constexpr int64_t kFewGrid = 256 / (kRowTile / kFewRows);
-hipError_t launch_contract(const CArgs &a, hipStream_t s) {
+// contract_few while its workgroups are at most one per compute unit of the stream: its LDS
+// holds one, and a second round costs more than contract_split's whole launch. Kernel times
+// (us, contract_few / contract_split) at 32 tiles of 128 x 128 and past them, 256 compute
+// units: n = 32 4.6 / 5.2 and 7.1 / 5.5 (48 tiles), n = 128 5.0 / 7.1 and 7.6 / 7.1, n = 512
+// 8.9 / 14.7 and 15.6 / 14.7, n = 2048 23 / 46 and 64 / 48 (96). The 192 compute units of a
+// fused step's value model: 24 tiles at n = 64 5.2 / 6.8, at n = 512 7.5 / 12.9; 32 tiles at
+// n = 64 7.5 / 7.0, at n = 256 9.8 / 9.1.
+hipError_t launch_contract(const CArgs &a, int cus, hipStream_t s) {
   const int64_t grid = (int64_t)a.nrowtiles * a.ntiles;
   if (grid <= 0) return hipSuccess;
   for (int t = 0; t < a.ntiles; ++t) {
@@ -1307,7 +1309,7 @@ hipError_t launch_contract(const CArgs &a, hipStream_t s) {
     if (tl.lin >= 0 && (!a.lin || tl.lin >= kColTile || (tl.lin & ~15) < tl.ncol))
       return hipErrorInvalidValue;
   }
-  if (grid <= kFewGrid) {
+  if (grid * (kRowTile / kFewRows) <= cus) {
     hipLaunchKernelGGL(contract_few, dim3((unsigned)(grid * (kRowTile / kFewRows))),
                        dim3(kFewThreads), 0, s, a);
     return hipGetLastError();

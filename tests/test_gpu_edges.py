@@ -243,6 +243,29 @@ def test_few_rows_bit_identical(name):
             assert torch.equal(small[k], big[k][:M]), (k, M)
 
 
+@pytest.mark.parametrize("name,M", [("C4", 1024), ("C4", 1025), ("C4", 1280), ("C4", 1281),
+                                    ("C3", 1536), ("C3", 1537), ("C3", 2048), ("C3", 2049)])
+def test_few_rows_fused(name, M):
+    """A fused step's value model has 3 (C4) or 2 (C3) column tiles on three quarters of the
+    compute units: on both sides of the few-rows contraction's limit there (24 tiles) and of
+    the one on the whole card (32), it gives the bits of a separate fit and scoring."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload(name, M)
+    space, model = _fit(w)
+    X, C = gp.to_device_columns(space, w.X), gp.to_device_columns(space, w.C)
+    y = torch.from_numpy(np.nan_to_num(w.y, nan=0.0)).cuda()
+    feas = torch.from_numpy(w.feasible).cuda()
+    ref = gp.score(model, C)
+    bufs = gp.FitScoreBuffers(space, len(w.y), M, with_cls=True)
+    gp.fit_score_into(space, X, y, feas, w.lengthscale, w.signal_var, w.noise_var,
+                      w.cls_signal_var, C, bufs)
+    out = bufs.result()
+    for k in ("mu", "sigma", "ei", "acq", "p_feas"):
+        assert torch.equal(out[k], ref[k]), k
+
+
 @pytest.mark.parametrize("d,n,count", [(1, 1, 1), (1, 2, 16), (7, 15, 17), (8, 16, 3), (9, 17, 33),
                                        (16, 33, 5), (17, 31, 15), (24, 65, 2), (25, 40, 64),
                                        (32, 50, 65), (33, 35, 4), (64, 48, 3)])
