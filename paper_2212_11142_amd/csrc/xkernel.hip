@@ -328,6 +328,8 @@ hipError_t launch_make_xobs(const uint32_t *codes, int32_t R, int32_t n, const X
   return hipGetLastError();
 }
 
+constexpr int64_t kNarrowWaves = 1024;  // wavefronts below which SIMDs (1024) stay idle
+
 int xkernel_splits(int64_t rows, int n) {
   constexpr int64_t kWaves = 1024;
   const int64_t waves = rows / 64;
@@ -353,16 +355,11 @@ hipError_t launch_xkernel(const XArgs &a0, int variant, const XSplit &sp, hipStr
     a.mu = sp.mu;
     a.sens = sp.sens;
   }
-  // A wavefront of cb candidate blocks reads each observation chunk once for all of them; in
-  // a launch that leaves SIMDs idle anyway one block per wavefront is faster, with the same
-  // arithmetic per candidate. Kernel times (us, one block / cb blocks) at so many wavefronts
-  // of cb: cb = 4, n = 512: 64 4.1 / 8.2, 256 5.4 / 8.9, 768 9.3 / 10.7, 1024 12.4 / 12.5;
-  // n = 128: 768 6.7 / 9.4, 1024 12.3 / 19.4; cb = 2, n = 1024: 128 4.8 / 5.9, 512 6.5 / 6.6,
-  // 640 8.1 / 7.2, 1024 11.0 / 8.7. The line for cb = 4 holds on the 192 compute units of a
-  // fused step's value model too (n = 512: 256 7.0 / 9.4, 1024 11.0 / 14.9).
-  const int cb = kVariants[variant].cb;
-  const bool narrow = !inspect && a.rows / (16 * cb) * ns <= 256 * cb;
-  const int cand_per_wave = 16 * (narrow ? 1 : cb);
+  // A wavefront of several candidate blocks reads each observation chunk once for all of
+  // them; in a launch that leaves SIMDs idle anyway one block per wavefront is faster (224
+  // rows against n = 512: 10.1 -> 7.0 us), with the same arithmetic per candidate.
+  const bool narrow = !inspect && a.rows / (16 * kVariants[variant].cb) * ns < kNarrowWaves;
+  const int cand_per_wave = 16 * (narrow ? 1 : kVariants[variant].cb);
   if (a.rows % cand_per_wave) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.rows / cand_per_wave), (unsigned)ns), block(64);
 #define BGP_XK(V, KS, NB, NE, ND, CB)                                                        \
