@@ -14,6 +14,8 @@
 // runs on fp16 MFMA with fp32 accumulation over operands split into high and low fp16
 // parts (three products per multiply-add), which keeps the accuracy of an fp32 product
 // at 16 times the fp32 MFMA rate.
+#include <algorithm>
+
 #include "common.h"
 #include "dist64.h"
 
@@ -1292,24 +1294,27 @@ __global__ __launch_bounds__(256) void gather_rows_split(const _Float16 *src, in
 
 }  // namespace
 
-// contract_few while its workgroups are at most one per compute unit of the stream: its LDS
-// holds one, and a second round costs more than contract_split's whole launch. Kernel times
-// (us, contract_few / contract_split) at 32 tiles of 128 x 128 and past them, 256 compute
-// units: n = 32 4.6 / 5.2 and 7.1 / 5.5 (48 tiles), n = 128 5.0 / 7.1 and 7.6 / 7.1, n = 512
-// 8.9 / 14.7 and 15.6 / 14.7, n = 2048 23 / 46 and 64 / 48 (96). The 192 compute units of a
-// fused step's value model: 24 tiles at n = 64 5.2 / 6.8, at n = 512 7.5 / 12.9; 32 tiles at
-// n = 64 7.5 / 7.0, at n = 256 9.8 / 9.1.
+// contract_few while its workgroups are at most one per compute unit of the stream (its LDS
+// holds one), or one and a half where the k-range is long: the second round then costs less
+// than contract_split's chain of chunks. Kernel times (us, contract_few / contract_split) by
+// tiles of 128 x 128, on 256 compute units: n = 32 32 4.6 / 5.3, 48 7.1 / 5.6; n = 256 32 6.5 /
+// 10.1, 48 11.0 / 10.4; n = 512 32 8.7 / 15.3, 42 12.8 / 15.2, 64 15.9 / 15.3; n = 2048 32 23 /
+// 46, 48 42 / 46, 80 63 / 47. On the 192 of a fused step's value model: k <= 192 24 6.0 / 9.0,
+// 32 9.7 / 9.0; k <= 384 24 7.3 / 13.0, 36 11.4 / 12.9, 72 17.4 / 13.0.
+constexpr int kFewLong = 384;
 hipError_t launch_contract(const CArgs &a, int cus, hipStream_t s) {
   const int64_t grid = (int64_t)a.nrowtiles * a.ntiles;
   if (grid <= 0) return hipSuccess;
+  int kmax = 0;
   for (int t = 0; t < a.ntiles; ++t) {
     const CTile &tl = a.tiles[t];
     if (tl.kend <= 0 || tl.kend % kKChunk || tl.kend > a.lda) return hipErrorInvalidValue;
     // a linear column lies in a sub-tile of its own, past the triangular columns
     if (tl.lin >= 0 && (!a.lin || tl.lin >= kColTile || (tl.lin & ~15) < tl.ncol))
       return hipErrorInvalidValue;
+    kmax = std::max(kmax, tl.kend);
   }
-  if (grid * (kRowTile / kFewRows) <= cus) {
+  if (grid * (kRowTile / kFewRows) <= (kmax >= kFewLong ? cus + cus / 2 : cus)) {
     hipLaunchKernelGGL(contract_few, dim3((unsigned)(grid * (kRowTile / kFewRows))),
                        dim3(kFewThreads), 0, s, a);
     return hipGetLastError();

@@ -243,12 +243,13 @@ def test_few_rows_bit_identical(name):
             assert torch.equal(small[k], big[k][:M]), (k, M)
 
 
-@pytest.mark.parametrize("name,M", [("C4", 1024), ("C4", 1025), ("C4", 1280), ("C4", 1281),
+@pytest.mark.parametrize("name,M", [("C4", 1024), ("C4", 1025), ("C4", 1536), ("C4", 1537),
                                     ("C3", 1536), ("C3", 1537), ("C3", 2048), ("C3", 2049)])
 def test_few_rows_fused(name, M):
     """A fused step's value model has 3 (C4) or 2 (C3) column tiles on three quarters of the
-    compute units: on both sides of the few-rows contraction's limit there (24 tiles) and of
-    the one on the whole card (32), it gives the bits of a separate fit and scoring."""
+    compute units: on both sides of the few-rows contraction's limits there (24 tiles, 36
+    where k is long) and on the whole card (32, 48), it gives the bits of a separate fit and
+    scoring."""
     import torch
 
     from paper_2212_11142_amd import gp
