@@ -711,7 +711,11 @@ constexpr int kRpRows = 32, kRpK = 64, kRpWaves = 8, kRpThreads = 64 * kRpWaves;
 constexpr int kRpStride = kRpK + 2;             // LDS row stride of the kernel values
 constexpr int kRpSets = kRpThreads / kRpRows;   // observations evaluated side by side
 constexpr int kRpObs = kRpK / kRpSets;          // observations per thread and chunk
-constexpr int kRpMaxBlocks = 8;                 // column blocks per wavefront at most
+// Column blocks per wavefront at most: more accumulators do not fit the registers, so past
+// kRpMaxCols columns the tall form takes over. At that line this form is well ahead (n_f =
+// 1024, this / tall: 4,097 candidates 241 / 414 us, 262,144 7.6 / 13.4 ms; n_f = 513, 4,097
+// 86 / 100 us; n_f = 600, 4,097, where the tall form's items fit one round, 107 / 99).
+constexpr int kRpMaxBlocks = 8;
 constexpr int kRpMaxCols = 16 * kRpWaves * kRpMaxBlocks;
 constexpr size_t kRpMaxLds = 150 * 1024;
 // LDS: kernel values, partial sums, two groups' candidate codes and the codes of `obs`
@@ -1178,8 +1182,9 @@ __global__ __launch_bounds__(256) void argmax_partial(const float *acq, int64_t 
 }
 
 // Small batches in one workgroup: a launch less than the two-step form, whose second launch
-// alone takes longer than one workgroup's pass over the values (a scoring of 4,096
-// candidates 35.6 -> 33.5 us).
+// alone takes longer than one workgroup's pass over the values (kernel times, us, one / the
+// first of two, the second 3.8 and the gap before it about 2: 4,096 values 5.2 / 3.1, 32,768
+// 6.1 / 3.4, 65,536 6.6 / 3.4, 131,072 9.8 / 3.5).
 constexpr int64_t kArgmaxSmall = 32768;
 constexpr int kArgmaxThreads = 1024;
 __global__ __launch_bounds__(kArgmaxThreads) void argmax_small(const float *acq, int M, int64_t *out) {

@@ -328,7 +328,7 @@ hipError_t launch_make_xobs(const uint32_t *codes, int32_t R, int32_t n, const X
   return hipGetLastError();
 }
 
-constexpr int64_t kNarrowWaves = 1024;  // wavefronts below which SIMDs (1024) stay idle
+constexpr int64_t kNarrowWaves = 1024;  // below so many wavefronts SIMDs (1024) stay idle
 
 int xkernel_splits(int64_t rows, int n) {
   constexpr int64_t kWaves = 1024;
@@ -356,8 +356,12 @@ hipError_t launch_xkernel(const XArgs &a0, int variant, const XSplit &sp, hipStr
     a.sens = sp.sens;
   }
   // A wavefront of several candidate blocks reads each observation chunk once for all of
-  // them; in a launch that leaves SIMDs idle anyway one block per wavefront is faster (224
-  // rows against n = 512: 10.1 -> 7.0 us), with the same arithmetic per candidate.
+  // them; in a launch that leaves SIMDs idle anyway one block per wavefront is faster, with
+  // the same arithmetic per candidate. Kernel times (us, one block / several) at so many
+  // wavefronts of several: four blocks, n = 512 256 5.6 / 8.6, 768 8.1 / 10.4, 1024 9.8 / 11.6;
+  // two blocks, n = 1024 384 5.8 / 7.7, 768 6.4 / 7.8, 2048 17 / 17. On the 192 compute units of
+  // a fused step's value model, four blocks, n = 512: 256 6.5 / 9.4, 768 9.9 / 12.6, 1536 56 /
+  // 60.
   const bool narrow = !inspect && a.rows / (16 * kVariants[variant].cb) * ns < kNarrowWaves;
   const int cand_per_wave = 16 * (narrow ? 1 : kVariants[variant].cb);
   if (a.rows % cand_per_wave) return hipErrorInvalidValue;

@@ -243,6 +243,23 @@ def test_few_rows_bit_identical(name):
             assert torch.equal(small[k], big[k][:M]), (k, M)
 
 
+def test_one_block_cross_kernel_bit_identical():
+    """The same for the cross-kernel with two candidate blocks per wavefront (permutations,
+    n = 2048) on both sides of its one-block form's limit: 384 and 512 rows in 64 splits are
+    768 and 1024 wavefronts. (mu is summed in as many parts as there are splits.)"""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload("C5", 4096)
+    _, model = _fit(w)
+    C = gp.to_device_columns(gp.Space(w.space), w.C)
+    big = gp.score(model, C)
+    for M in (1, 128, 129, 384, 385, 512, 513):
+        small = gp.score(model, [c[:M].contiguous() for c in C])
+        assert torch.equal(small["sigma"], big["sigma"][:M]), M
+        assert float((small["mu"] - big["mu"][:M]).abs().max()) <= 4e-7 * float(big["mu"].abs().max())
+
+
 @pytest.mark.parametrize("name,M", [("C4", 1024), ("C4", 1025), ("C4", 1536), ("C4", 1537),
                                     ("C3", 1536), ("C3", 1537), ("C3", 2048), ("C3", 2049)])
 def test_few_rows_fused(name, M):
