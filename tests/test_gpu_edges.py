@@ -85,6 +85,28 @@ def test_start_selection_blocks(M, k):
     test_start_selection(M, k)
 
 
+@pytest.mark.parametrize("order", ["drawn", "ascending"])
+@pytest.mark.parametrize("M", [262145, 600001])
+def test_start_selection_many_batches(M, order):
+    """Ranges of more than one batch per block: the threshold that a block keeps, and its
+    sort before the range ends; ascending values pass every threshold."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    w = make_workload("C1", M, n=20)
+    space, model = _fit(w)
+    Cc = gp.to_device_columns(space, w.C)
+    if order == "ascending":
+        by = torch.argsort(gp.score(model, Cc)["acq"], stable=True)
+        Cc = [c[by].contiguous() for c in Cc]
+    acq = gp.score(model, Cc)["acq"].cpu().numpy()
+    want = np.lexsort((np.arange(M), -acq))
+    for k in (1, 7, 64):
+        out = gp.local_search(model, Cc, n_starts=k, max_steps=0)
+        assert np.array_equal(out["start_index"].cpu().numpy(), want[:k])
+        assert np.array_equal(out["acq"].cpu().numpy(), acq[want[:k]])
+
+
 @pytest.mark.parametrize("sizes", [[1], [2], [4], [5], [6], [7], [39], [41], [300000],
                                    [1, 5, 5000, 200000]])
 def test_chain_membership_tables(sizes):
@@ -336,6 +358,50 @@ def test_refine_block_sizes(n):
             if k != "mu":  # eps n cond of the cancellation, in units of sigma
                 tol = tol + 1e-14 * n / p["sigma"].double().clamp(min=1e-3)
             assert bool(((x - y).abs() <= tol).all()), (k, a, float((x - y).abs().max()))
+
+
+@pytest.mark.parametrize("n_real,n", [(40, 65), (30, 200), (30, 256), (16, 389), (16, 512), (24, 300),
+                                      (40, 1000)])
+def test_refine_block_streamed(n_real, n):
+    """The same where the observations' codes do not stay in LDS: a chunk's are loaded between
+    the phases, the next group's candidates beside them (not with the most column blocks).
+    Noise 1e-2 keeps sigma^2 above 1e-3 of the signal variance: the sum of squares cancels
+    n eps / 1e-3 at most, below the fp32 rounding of the outputs (6e-8, for mu of its sum's
+    terms)."""
+    import torch
+
+    from paper_2212_11142_amd import gp
+    from workloads import Param
+    params = ([Param(f"r{q}", "real") for q in range(n_real)]
+              + [Param("c", "cat", levels=5), Param("p", "perm", m=5)])
+    ni, obs = 2, (n + 63) // 64 * 64  # words of the codes besides the numeric ones, at least
+    lds = 8 * (32 * 66 + 24 * 32 + n_real * (64 + obs)) + 4 * ni * (64 + obs)
+    assert lds > 78 * 1024  # (not resident)
+    rng = np.random.default_rng(n)
+    M = 4096 + 33
+
+    def draw(count):
+        cols = [rng.random(count) for _ in range(n_real)]
+        cols.append(rng.integers(0, 5, count).astype(np.int32))
+        cols.append(np.argsort(rng.random((count, 5)), axis=1).astype(np.int32))
+        return cols
+
+    space = gp.Space(params)
+    X, C = gp.to_device_columns(space, draw(n)), gp.to_device_columns(space, draw(M))
+    y = torch.from_numpy(rng.normal(size=n)).cuda()
+    feas = torch.ones(n, dtype=torch.uint8, device="cuda")
+    model = gp.fit(space, X, y, feas, np.full(n_real + 2, np.sqrt(n_real + 2) / 2), 1.0, 1e-2, None)
+    gp.debug_set_refine(model, float("inf"), -1.0)
+    big = gp.score(model, C)
+    assert float(big["sigma"].min()) ** 2 > 1e-3
+    assert gp.refined_count(model, big["_buffers"]) == M
+    scale = float(big["mu"].abs().max())
+    for a in (0, 2000, M - 100):
+        p = gp.score(model, [c[a:a + 100].contiguous() for c in C])
+        for k in ("mu", "sigma", "ei"):
+            x, r = big[k][a:a + 100].double(), p[k].double()
+            tol = 4e-7 * (torch.full_like(r, scale) if k == "mu" else r.abs() + 1e-7)
+            assert bool(((x - r).abs() <= tol).all()), (k, a, float((x - r).abs().max()))
 
 
 @pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 1023, 1025, 32767, 32768, 32769])
