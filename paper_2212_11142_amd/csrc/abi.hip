@@ -433,7 +433,7 @@ ScorePlan plan_score(Carver &cv, int R, int lda, int ntiles, int n_f, int n, int
   P.rpart = cv.take<double>((int64_t)kRefineSplitGroups * nr * 8);
   P.rmup = cv.take<double>((int64_t)kRefineSplitGroups * 8);
   if (rows > kRefineBlockMin) {
-    P.rpart64 = cv.take<double>((int64_t)refine_block_tiles(n_f) * rows);
+    P.rpart64 = cv.take<double>((int64_t)((n_f + kRefineBlockCols - 1) / kRefineBlockCols) * rows);
     P.rmu64 = cv.take<double>(rows);
   }
   P.amax_v = cv.take<float>(kArgmaxBlocks);

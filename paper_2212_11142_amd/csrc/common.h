@@ -189,7 +189,7 @@ struct RArgs {
   float *mu, *sigma, *ei, *p_feas, *acq;
   double *part;             // split path: [groups][ceil(n_f / 64)][cb] partial |v|^2
   double *mup;              // split path: [groups][cb] mu
-  double *part64;           // block path: [refine_block_tiles(n_f)][cap] partial |v|^2
+  double *part64;           // block path: [ceil(n_f / 256)][cap] partial |v|^2
   double *mu64;             // block path: [cap] mu
   int64_t cap;              // flagged candidates the block path's buffers hold (>= count)
 };
@@ -313,7 +313,6 @@ hipError_t launch_epilogue_cls(const EArgs &a, float *pwork, hipStream_t s);
 // both of the above in one kernel (when they share a stream)
 hipError_t launch_epilogue(const EArgs &a, float *pwork, hipStream_t s);
 int refine_candidates_per_block(int n_f);
-int refine_block_tiles(int n_f);  // partial sums per candidate of the block path; grows with n_f
 // fp64 recomputation of the flagged candidates: the block path's products (more than
 // kRefineBlockMin flagged; needs the value model only; cus: compute units the stream
 // can use), then the rest, which writes every output of the flagged candidates (needs

@@ -59,18 +59,6 @@ def test_workspace_sizes(lib, name):
     assert lib.gp_fit_score_workspace_bytes(sp.ref(), 0, 1, 10) == 0
 
 
-@pytest.mark.parametrize("n0,n1,more", [(256, 512, 0), (512, 1024, 0), (1024, 2048, 7), (2048, 4096, 8)])
-def test_scoring_workspace_per_candidate(lib, n0, n1, more):
-    """Bytes per candidate between two observation counts: the split kernel row (4 n), a
-    contraction partial per 128 columns (4 bytes), and the recomputation's partials (8
-    bytes): one up to 1024 columns, then one per 256."""
-    sp = space_of("C2")
-    M0, rows = 1 << 20, 1 << 16
-    f = lambda n, M: lib.gp_fit_score_workspace_bytes(sp.ref(), n, 0, M)  # noqa: E731
-    per = lambda n: f(n, M0 + rows) - f(n, M0)  # noqa: E731
-    assert per(n1) - per(n0) == rows * (4 * (n1 - n0) + 4 * (n1 - n0) // 128 + 8 * more)
-
-
 def test_fused_workspace_bound_any_lengthscales(lib):
     """gp_fit_score_workspace_bytes takes no lengthscales, so its scoring region must hold
     the candidate codes for any of them. Categorical one-hot fields share a 32-bit code
