@@ -11,6 +11,7 @@ Prints one JSON line. The default workload is the FPGA-pragma-shaped space
 (d = 20, n = 512 observations, 30% infeasible, M = 1,048,576 candidates).
 """
 import argparse
+import gc
 import hashlib
 import json
 import math
@@ -70,6 +71,14 @@ def measured_traffic(record_path, workload):
     fetch = rec["fetch_kib_per_step"] * 1024 * rec["fetch_scale"]
     write = rec["write_kib_per_step"] * 1024 * rec["write_scale"]
     return fetch + write, "rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated"
+
+
+def settle_interpreter():
+    """Collects what the set-up left and takes every live object out of later collections: a
+    full one over the modules' objects takes 37-41 ms, thirty times the five steps of the
+    shortest workload."""
+    gc.collect()
+    gc.freeze()
 
 
 def calibrate_copy():
@@ -213,6 +222,7 @@ def main():
         return gp.fit_score_into(space, X, y, feas, w.lengthscale, w.signal_var, w.noise_var,
                                  w.cls_signal_var, Cc, fbufs, mask, w.eps_f)
 
+    settle_interpreter()
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
@@ -400,8 +410,9 @@ def time_forest(gp, space, X, feas, Cc, n_trees, reps=3):
 
 def time_other_workloads(gp, names, steps=5, warmup=2):
     """Extra (parity configurations, not the headline): the same fused step (gp_fit_score)
-    on the other full-size workloads, wall clock over `steps` steps, with the number of
-    candidates the last step recomputed in fp64."""
+    on the other full-size workloads, wall clock over `steps` steps, with the time until
+    each step's call returned (it waits for its fit) and the number of candidates the last
+    step recomputed in fp64."""
     import torch
     from workloads import make_workload
     out = {}
@@ -420,17 +431,20 @@ def time_other_workloads(gp, names, steps=5, warmup=2):
             return gp.fit_score_into(space, X, y, feas, w.lengthscale, w.signal_var,
                                      w.noise_var, w.cls_signal_var, Cc, fb, mask, w.eps_f)
 
+        settle_interpreter()
         for _ in range(warmup):
             step()
         torch.cuda.synchronize()
-        t0 = time.perf_counter()
+        at = [time.perf_counter()]
         for _ in range(steps):
             m = step()
+            at.append(time.perf_counter())
         torch.cuda.synchronize()
-        ms = (time.perf_counter() - t0) * 1e3 / steps
+        ms = (time.perf_counter() - at[0]) * 1e3 / steps
         info = m.info()
         out[name] = {"workload": WORKLOAD_TEXT[name], "n": info["n"],
                      "n_feasible": info["n_feasible"], "M": w.M, "ms_per_step": ms,
+                     "step_return_ms": [round((b - a) * 1e3, 4) for a, b in zip(at, at[1:])],
                      "candidates_per_s": w.M / (ms * 1e-3),
                      "refined_fp64": gp.refined_count(m, fb)}
         del fb, X, Cc
