@@ -158,13 +158,18 @@ __global__ __launch_bounds__(256) void cot_sample_k(const CotDesc *dd, const uin
 // kCotBucket keys, kCotFill on average at most, and a full bucket's further keys go to the
 // next one, so a lookup reads buckets until it finds the key or a free slot.
 constexpr uint64_t kCotEmpty = ~0ull;  // (a key of 64 one bits is looked up in the key table)
-__device__ __forceinline__ int64_t cot_bucket(uint64_t key, int64_t n) {
+__device__ __forceinline__ uint64_t cot_mix(uint64_t key) {
   uint64_t h = key * 0x9E3779B97F4A7C15ull;  // 2^64 / golden ratio
   h ^= h >> 32;
-  h *= 0x9E3779B97F4A7C15ull;
-  return (int64_t)__umul64hi(h, (uint64_t)n);
+  return h * 0x9E3779B97F4A7C15ull;
+}
+__device__ __forceinline__ int64_t cot_bucket(uint64_t key, int64_t n) {
+  return (int64_t)__umul64hi(cot_mix(key), (uint64_t)n);
 }
 
+// A key tries its bucket's slots from one that its hash names, so that a bucket's keys seldom
+// wait for each other's slots (908,759 keys: 105 -> 74 us; 9,339,902: 453 -> 423, bound by
+// the random lines).
 __global__ __launch_bounds__(256) void cot_hash_k(const uint64_t *keys, int64_t n, int64_t nb,
                                                    uint64_t *buckets) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -172,11 +177,14 @@ __global__ __launch_bounds__(256) void cot_hash_k(const uint64_t *keys, int64_t 
   const uint64_t key = keys[i];
   if (key == kCotEmpty) return;
   int64_t b = cot_bucket(key, nb);
+  const int q0 = (int)(cot_mix(key) % kCotBucket);
   // n < nb kCotBucket keys: a free slot exists (nb + 1 buckets are looked at in the end)
   for (int64_t step = 0; step <= nb; ++step) {
     unsigned long long *s = reinterpret_cast<unsigned long long *>(buckets + b * kCotBucket);
-    for (int q = 0; q < kCotBucket; ++q)
-      if (s[q] == kCotEmpty && atomicCAS(s + q, kCotEmpty, (unsigned long long)key) == kCotEmpty) return;
+    for (int q = 0; q < kCotBucket; ++q) {
+      unsigned long long *at = s + (q0 + q) % kCotBucket;
+      if (*at == kCotEmpty && atomicCAS(at, kCotEmpty, (unsigned long long)key) == kCotEmpty) return;
+    }
     b = b + 1 == nb ? 0 : b + 1;
   }
 }
