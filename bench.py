@@ -377,7 +377,8 @@ def time_hyperfit(gp, w, space, X, y, feas, n_samples, n_starts, n_f, reps=3):
             "best_objective": float(out["value"].max()),
             "batch64_value_grad_ms": b_ms, "batch64_fp64_tflops": tf,
             "batch64_frac_of_fp64_peak": tf / FP64_PEAK_TFLOPS,
-            "bound": "latency (one launch per 32-column block of the factorisation)"}
+            "bound": "block products of the batched factorisation (three per trailing block); "
+                     "the fit: its chain of dependent evaluations"}
 
 
 def time_forest(gp, space, X, feas, Cc, n_trees, reps=3):

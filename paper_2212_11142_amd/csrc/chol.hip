@@ -106,11 +106,11 @@ __device__ __forceinline__ double sel4(double a, double b, double c, double d, i
 // v_mfma_f64_4x4x4f64 per tile (its four blocks are the tile's four row groups), and the
 // trailing tiles lose X D^-1 X^T. The scaled panels X D^-1/2 are L and L^-T.
 //
-// What bounds it is the chain (per panel: 20 lane reads, four pivots of 60 cycles, two MFMA
-// latencies of 28 and 92 cycles): about 7,000 cycles per block, against 16,800 for the form
-// it replaced, in which 256 threads shared the block through LDS with a barrier per panel.
-// Every panel is unrolled: as a loop over register-shifted tiles, for a smaller instruction
-// footprint, it took 4.7 us where this takes 3.6.
+// What bounds it is the chain of 32 pivots. Kernel times: chol_panel (one block's load,
+// factorisation and stores) 5.9 us, a trailing launch of a single matrix 7.4; 9.2 and 11.3
+// with the form it replaced, in which 256 threads shared the block through LDS with a
+// barrier per panel. Every panel is unrolled: as a loop over register-shifted tiles, for a
+// smaller instruction footprint, the block took 1.1 us longer.
 #define BGP_MFMA16(A, B, C) __builtin_amdgcn_mfma_f64_16x16x4f64(A, B, C, 0, 0, 0)
 #define BGP_MFMA4(A, B) __builtin_amdgcn_mfma_f64_4x4x4f64(A, B, 0.0, 0, 0, 0)
 struct BlockPanel {

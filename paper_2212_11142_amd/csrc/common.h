@@ -189,7 +189,8 @@ struct RArgs {
   float *mu, *sigma, *ei, *p_feas, *acq;
   double *part;             // split path: [groups][ceil(n_f / 64)][cb] partial |v|^2
   double *mup;              // split path: [groups][cb] mu
-  double *part64;           // block path: [ceil(n_f / 256)][cap] partial |v|^2
+  double *part64;           // block path: partial |v|^2, [cap] up to 1,024 columns, else
+                            // [ceil(n_f / 256)][cap] (which is allocated for every n_f)
   double *mu64;             // block path: [cap] mu
   int64_t cap;              // flagged candidates the block path's buffers hold (>= count)
 };
@@ -333,7 +334,7 @@ hipError_t launch_gather_rows_split(const uint16_t *src, int32_t lda, float inv_
 // A setting theta = (log l_1..log l_d, log s, t), noise variance = floor + e^t.
 constexpr int kHypBatch = 64;        // settings per batched evaluation
 constexpr int kHypMaxD = kMaxD + 2;  // entries of a setting
-constexpr int kHypGradChunk = 32;    // lengthscale gradients accumulated per launch plane
+constexpr int kHypGradChunk = 32;    // lengthscale gradients per row of the partial sums
 constexpr int kLbfgsMem = 10;        // stored (s, y) pairs
 constexpr int kHypGradBlocks = 128;  // pair-range blocks of the gradient contraction
 constexpr int kLbfgsMaxHalvings = 30;  // step halvings before a line search gives up
@@ -441,7 +442,7 @@ hipError_t launch_cot_member(const CotDesc *dd, const uint64_t *keys, const uint
 // Hidden constraints (Sec. 4.2): a classification forest of CART trees on bootstrap
 // samples of the observations; features are REAL/INT values, ORD/CAT indices and PERM
 // positions (one per item), stored as fp64.
-constexpr int kForestMaxF = 120;     // features (prediction keeps a wavefront's 64 x F 16-bit ranks in LDS)
+constexpr int kForestMaxF = 120;     // features (prediction keeps a wavefront's 64 x F values or ranks in LDS)
 constexpr int kForestMaxMtry = 16;   // features tried per node (floor(sqrt(F)))
 struct ForestDesc {
   int32_t d, F, n, n_trees, max_depth, min_split, mtry, cap;  // cap: nodes per tree (2n)

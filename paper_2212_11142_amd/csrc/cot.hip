@@ -5,7 +5,7 @@
 //
 // A tree's leaves are kept as sorted 64-bit keys packing their value indices into bit
 // fields (first level most significant), so a draw is one multiply-high, one key load
-// and shifts, and a membership test is a binary search. Random words come from Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC 2011),
+// and shifts, and a membership test is a hash lookup. Random words come from Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC 2011),
 // key (seed, 0), counter (offset + j, b, 0, 0) for the b-th block of four words of
 // configuration j; words are used in order: one per tree, then per free parameter in
 // space order one word (REAL, INT, ORD, CAT) or m - 1 words (PERM).

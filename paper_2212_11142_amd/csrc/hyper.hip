@@ -292,7 +292,8 @@ __global__ __launch_bounds__(256) void hyp_grad_k(const HypArgs a, int B, const 
 #pragma unroll
   for (int q = 0; q < PT; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
   double acc_s = 0.0, acc_n = 0.0;
-  // (every wavefront runs the same number of rounds: the pairs past the end have C = 0)
+  // (a wavefront's own loop without workgroup barriers: its wavefronts may differ by a
+  // round; in a last round the pairs past the end have C = 0)
   const int64_t step = (int64_t)gridDim.x * 4 * kGradPairs;
   const int64_t q0 = ((int64_t)blockIdx.x * 4 + w) * kGradPairs;
   for (int64_t q = q0; q < npairs; q += step) {
