@@ -2380,7 +2380,8 @@ ForestPlan plan_forest(Carver &cv, const Layout &L, int n, int F, int T) {
   ForestPlan P{};
   P.desc = cv.take<ForestDesc>(1);
   P.nodes = cv.take<ForestNode>((int64_t)T * 2 * n);
-  P.nnodes = cv.take<int32_t>(T);
+  P.nnodes = cv.take<int32_t>((int64_t)T + F);  // and each feature's distinct values (nd)
+  P.nd = P.nnodes + T;
   P.penc = cv.take<ParamEnc>(L.d);
   P.table = cv.take<double>((int64_t)L.table.size());
   P.codes = cv.take<uint32_t>((int64_t)n * L.R);
@@ -2388,7 +2389,6 @@ ForestPlan plan_forest(Carver &cv, const Layout &L, int n, int F, int T) {
   P.X = cv.take<double>((int64_t)F * n);
   P.val = cv.take<double>((int64_t)F * n);
   P.rank = cv.take<uint16_t>((int64_t)F * n);
-  P.nd = cv.take<int32_t>(F);
   P.pack = cv.take<uint64_t>((int64_t)T * 2 * n);
   P.lofs = cv.take<int32_t>(T);
   P.bstart = cv.take<int32_t>(T + 1);
@@ -2478,8 +2478,8 @@ gp_status gp_forest_fit(const gp_space *space, const void *const *X_cols, int32_
     HIPCHK(launch_forest_train(P.desc, f->h, P.rank, P.val, P.nd, feasible, P.nodes, P.pack, P.aux,
                                P.nnodes, s));
     // prediction's batches: consecutive trees whose nodes fit its LDS together
-    std::vector<int32_t> nn((size_t)n_trees), lofs((size_t)n_trees), bstart;
-    HIPCHK(hipMemcpyAsync(nn.data(), P.nnodes, sizeof(int32_t) * n_trees, hipMemcpyDeviceToHost, s));
+    std::vector<int32_t> nn((size_t)n_trees + f->h.F), lofs((size_t)n_trees), bstart;
+    HIPCHK(hipMemcpyAsync(nn.data(), P.nnodes, sizeof(int32_t) * nn.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     const int64_t room = forest_tree_words(f->h.F);
     int64_t used = 0, most = 1;
@@ -2496,7 +2496,11 @@ gp_status gp_forest_fit(const gp_space *space, const void *const *X_cols, int32_
     HIPCHK(hipMemcpyAsync(P.lofs, lofs.data(), sizeof(int32_t) * n_trees, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(P.bstart, bstart.data(), sizeof(int32_t) * bstart.size(), hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));
-    f->trees = ForestTrees{P.pack, P.nnodes, P.lofs, P.bstart, (int32_t)bstart.size() - 1, most, P.val, P.nd};
+    int32_t steps = 0;
+    for (size_t q = (size_t)n_trees; q < nn.size(); ++q)
+      for (int32_t v = nn[q]; v > 0; v >>= 1) ++steps;
+    f->trees = ForestTrees{P.pack, P.nnodes, P.lofs, P.bstart, (int32_t)bstart.size() - 1, most, P.val, P.nd,
+                           steps};
     f->d_desc = P.desc;
     f->d_nodes = P.nodes;
     f->d_nnodes = P.nnodes;

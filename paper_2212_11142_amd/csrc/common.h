@@ -475,6 +475,7 @@ struct ForestTrees {
   int64_t tree_words;
   const double *val;
   const int32_t *nd;
+  int32_t rank_steps;  // of the binary searches of all features together
 };
 constexpr size_t kForestLds = 156 * 1024;  // prediction: trees and ranks
 // wavefronts per prediction workgroup at most: their ranks take up to 64 KB of the LDS

@@ -542,18 +542,27 @@ hipError_t launch_forest_train(const ForestDesc *dd, const ForestDesc &hd, const
   return hipGetLastError();
 }
 
-// Where the direct kernel is the faster one (us a call, direct / staged; F = 20 unless said).
-// Up to 512 configurations per compute unit latency counts, and a tree's walk stands against
-// a feature's search: 65,536 configurations, n = 512, 1 tree 13 / 18, 8 trees 21 / 25, 16
-// trees 32 / 33, 64 trees 100 / 86; F = 24, 16 trees of n = 24 18 / 25; F = 5, 8 trees 18 /
-// 18, 16 trees 30 / 27. Beyond that the loads of the walks count: 1,048,576 configurations,
-// n = 512, 2 trees 91 / 101, 4 trees 108 / 110, 8 trees 143 / 127; F = 5, 8 trees 59 / 85. A
-// single configuration reads one path of each tree, and staging reads the whole tree: n =
-// 4096, 2,000 trees 2.5 / 4.0 ms; n = 512 1.5 / 1.35.
-bool forest_direct(int64_t M, const ForestDesc &hd, int cus) {
+// Where the direct kernel is the faster one. The staged one searches every feature's distinct
+// values (rank_steps loads one after the other) before its walks, which are then cheaper; a
+// walk takes about log2 n steps. Times of a call (us, direct / staged, n = 512 unless said):
+//   up to 8 wavefronts per compute unit, or as many as the features' values in LDS leave
+//   room for, latency counts: 65,536 configurations, 20 features of 58 steps: 1 tree 13 / 18,
+//   8 21 / 25, 16 32 / 33, 64 100 / 86; 24 features of 88: 16 trees 32 / 38, 32 57 / 55; 5 of
+//   32: 8 18 / 18, 16 30 / 27; 40 of 400: 64 135 / 153, 112 222 / 222; 24 of 78 at n = 24, 32
+//   trees 27 / 33;
+//   with more of them the loads of the walks do: 1,048,576 configurations, 20 features: 2 trees
+//   91 / 101, 4 108 / 110, 8 143 / 127; 262,144: 2 27 / 26, 4 33 / 29; 65,536 of 120 features of
+//   480 steps: 16 trees 109 / 117, 32 171 / 139; few features leave room for more wavefronts:
+//   1,048,576 of 5 features: 8 trees 59 / 85, 16 103 / 122.
+// A single configuration reads one path of each tree, where staging reads the whole trees: n =
+// 4096, 2,000 trees 2.5 / 4.0 ms (n = 512 1.5 / 1.35).
+bool forest_direct(int64_t M, const ForestDesc &hd, int rank_steps, int cus) {
   if (M == 1 && hd.n >= 3072) return true;
-  if (M <= (int64_t)512 * cus) return hd.n_trees <= std::min(std::max(hd.F, 8), 24);
-  return hd.n_trees * hd.F <= 40;
+  const int64_t walks = (int64_t)hd.n_trees * (32 - __builtin_clz((unsigned)hd.n));
+  const int64_t lds = (int64_t)sizeof(double) * 64 * hd.F + sizeof(ForestDesc) + sizeof(CotCols);
+  const int64_t waves = std::min<int64_t>(8, 160 * 1024 / lds);
+  if (M <= 64 * waves * cus) return 2 * walks <= 5 * (int64_t)rank_steps;
+  return 20 * walks <= 7 * (int64_t)rank_steps || hd.n_trees * hd.F <= 48;
 }
 
 hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, const ForestNode *nodes,
@@ -563,7 +572,7 @@ hipError_t launch_forest_predict(const ForestDesc *dd, const ForestDesc &hd, con
                                  hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (cus < 1) return hipErrorInvalidValue;
-  if (forest_direct(M, hd, cus)) {
+  if (forest_direct(M, hd, tr.rank_steps, cus)) {
     hipLaunchKernelGGL(forest_predict_direct_k, dim3((unsigned)((M + 63) / 64)), dim3(64),
                        sizeof(double) * 64 * (size_t)hd.F, s, dd, nodes, cols, M, ei, mask, eps_f,
                        p, acq);

@@ -198,9 +198,9 @@ def test_forest_sizes(n, trees, depth, min_split):
 
 
 @pytest.mark.parametrize("name,n,trees,M", [
-    ("C5", 300, 1, 4099), ("C5", 300, 24, 4099), ("C5", 300, 25, 4099),
-    ("C1", 200, 8, 4099), ("C1", 200, 9, 4099), ("C1", 200, 8, 131072), ("C1", 200, 8, 131073),
-    ("C1", 200, 9, 131073), ("C1", 3071, 30, 1), ("C1", 3072, 30, 1),
+    ("C5", 300, 1, 4099), ("C5", 300, 20, 4099), ("C5", 300, 40, 4099), ("C5", 300, 3, 131073),
+    ("C5", 300, 4, 131073), ("C1", 200, 9, 4099), ("C1", 200, 12, 4099), ("C1", 200, 9, 131072),
+    ("C1", 200, 9, 131073), ("C1", 200, 10, 131073), ("C1", 3071, 30, 1), ("C1", 3072, 30, 1),
     ("C1", 1024, 129, 5003), ("C1", 1024, 129, 262144 + 65)])
 def test_forest_prediction_routes(name, n, trees, M):
     """Predictions on both sides of the rule between walks through the caches and through
